@@ -1,0 +1,257 @@
+// Tables of the q-gram filter (host only).
+//
+// Wu-Manber's SHIFT and HASH (Section 3.2) look at one block per window and
+// move on by a data-dependent shift; each lane's windows form a serial chain.
+// Here the blocks that are looked at are the same for every text: the q-grams
+// at multiples of t. A gram that occurs in no string at an offset below t
+// rules out the t starting positions that end at it, so most text is read
+// once and answered by one bit of an LDS table per t bytes, all of them
+// independent. The grams that remain carry their (string, offset) pairs with
+// the codes of the string's first 16 characters, as Wu-Manber's HASH and
+// PREFIX do, and whatever passes those is compared byte by byte.
+#include <math.h>
+#include <string.h>
+
+#include <algorithm>
+#include <vector>
+
+#include "mpm_internal.h"
+
+namespace mpm {
+
+namespace {
+
+const uint32_t Q_MAX = 10;        // 4^10 bits = 128 KiB of the 160 KiB LDS
+const uint32_t CHAIN_MAX = 64;    // entries of one gram
+const uint32_t NONE = 0xffffffffu;
+
+template <typename T>
+uint64_t append(std::vector<uint8_t> &img, const T *src, uint64_t count)
+{
+    const uint64_t off = (img.size() + 255) / 256 * 256;
+    img.resize((off + count * sizeof(T) + 15) / 16 * 16, 0);
+    if (count)
+        memcpy(img.data() + off, src, count * sizeof(T));
+    return off;
+}
+
+// The shift whose codes (b >> shift) & 3 two random pattern characters share
+// least often (frequent bytes get codes of their own); freq receives the byte
+// counts, share the codes' shares.
+uint32_t code_shift_of(const std::vector<uint8_t> &bytes, double *freq, double *share)
+{
+    std::fill(freq, freq + 256, 0.0);
+    for (uint8_t b : bytes)
+        freq[b] += 1.0;
+    uint32_t sh = 0;
+    double best = 1e300;
+    for (uint32_t s = 0; s < 7; s++) {
+        double mass[4] = {0, 0, 0, 0}, c = 0;
+        for (uint32_t b = 0; b < 256; b++)
+            mass[(b >> s) & 3u] += freq[b];
+        for (double x : mass)
+            c += x * x;
+        if (c < best * (1 - 1e-12)) {
+            best = c;
+            sh = s;
+            for (int k = 0; share && k < 4; k++)
+                share[k] = mass[k] / (double)bytes.size();
+        }
+    }
+    return sh;
+}
+
+struct Strings {
+    const mpm_index *ix;
+    const uint8_t *at(uint32_t u) const
+    {
+        return ix->upats.data() + (ix->var ? ix->upoff[u] : (uint64_t)u * ix->m);
+    }
+    uint32_t len(uint32_t u) const { return ix->var ? ix->upoff[u + 1] - ix->upoff[u] : ix->m; }
+};
+
+// Codes of the first t + q - 1 <= 25 characters of every string.
+std::vector<uint64_t> head_codes(const mpm_index *ix, const Strings &S, uint32_t sh)
+{
+    std::vector<uint64_t> h(ix->du);
+    for (uint32_t u = 0; u < ix->du; u++) {
+        const uint8_t *p = S.at(u);
+        const uint32_t k = std::min<uint32_t>(S.len(u), 25);
+        uint64_t x = 0;
+        for (uint32_t j = 0; j < k; j++)
+            x |= (uint64_t)((p[j] >> sh) & 3u) << (2 * j);
+        h[u] = x;
+    }
+    return h;
+}
+
+// Expected candidates and chain steps per text byte when text characters
+// follow the code shares of the strings' characters.
+struct Rate {
+    double cand, steps;
+    uint32_t longest;
+};
+
+Rate rate_of(const std::vector<uint64_t> &head, uint32_t q, uint32_t t, const double *share,
+             std::vector<uint8_t> &count)
+{
+    // the share of a gram: a product of two table entries
+    const uint32_t q1 = std::min<uint32_t>(q, 5), q2 = q - q1;
+    std::vector<double> lo(1u << (2 * q1)), hi(1u << (2 * q2));
+    for (size_t k = 0; k < 2; k++) {
+        std::vector<double> &v = k ? hi : lo;
+        const uint32_t len = k ? q2 : q1;
+        for (uint32_t g = 0; g < v.size(); g++) {
+            v[g] = 1;
+            for (uint32_t j = 0; j < len; j++)
+                v[g] *= share[(g >> (2 * j)) & 3u];
+        }
+    }
+    count.assign(1ull << (2 * q), 0);
+    Rate r = {0, 0, 0};
+    const uint32_t mask = (1u << (2 * q)) - 1u, m1 = (uint32_t)lo.size() - 1;
+    for (uint64_t h : head)
+        for (uint32_t off = 0; off < t; off++) {
+            const uint32_t g = (uint32_t)(h >> (2 * off)) & mask;
+            const double pr = lo[g & m1] * hi[g >> (2 * q1)];
+            r.steps += pr;
+            if (count[g] == 0)
+                r.cand += pr;
+            if (count[g] < 255)
+                count[g]++;
+            r.longest = std::max<uint32_t>(r.longest, count[g]);
+        }
+    r.cand /= t;
+    r.steps /= t;
+    return r;
+}
+
+// Cost per text byte in vector instructions of a lane: packing, lookups
+// (about six each) and batches of 64 candidates (about 120 each, plus their
+// chain steps); a 128 KiB table halves the waves of a CU.
+double cost_of(uint32_t q, uint32_t t, double cand, double steps)
+{
+    return (1.2 + 6.0 / t + 120.0 * cand + 20.0 * steps) * (q == Q_MAX ? 1.25 : 1.0);
+}
+
+}  // namespace
+
+// Choose q and t, and append the tables to the index's device image; leaves
+// gram.ok = 0 when the set has no useful filter.
+void build_gram(mpm_index *ix)
+{
+    mpm_index::Gram &G = ix->gram;
+    const uint32_t m = ix->m;
+    if (m < 4 || ix->du == 0 || ix->du >= (1u << 28))
+        return;
+    const Strings S = {ix};
+    double freq[256], share[4];
+    const uint32_t sh = code_shift_of(ix->upats, freq, share);
+    // The cheapest (t, q), by the cost if grams were spread evenly; the first
+    // few are then counted.
+    struct Choice {
+        double cost;
+        uint32_t tl, q;
+    };
+    std::vector<Choice> all;
+    for (uint32_t tl = 0; tl <= 4; tl++) {
+        const uint32_t t = 1u << tl;
+        for (uint32_t q = 4; q <= Q_MAX && q + t - 1 <= m; q++) {
+            const double even = (double)ix->du / (double)(1ull << (2 * q));
+            all.push_back({cost_of(q, t, (1.0 - exp(-even * t)) / t, even), tl, q});
+        }
+    }
+    std::stable_sort(all.begin(), all.end(), [](const Choice &x, const Choice &y) { return x.cost < y.cost; });
+    const std::vector<uint64_t> head = head_codes(ix, S, sh);
+    std::vector<uint8_t> count;
+    double best = 1e300;
+    uint32_t bq = 0, bt = 0;
+    for (size_t k = 0; k < all.size() && k < 4 && all[k].cost < std::min(0.9 * best, 25.0); k++) {
+        const Rate r = rate_of(head, all[k].q, 1u << all[k].tl, share, count);
+        if (r.longest > CHAIN_MAX)
+            continue;
+        const double c = cost_of(all[k].q, 1u << all[k].tl, r.cand, r.steps);
+        if (c < best) {
+            best = c;
+            bq = all[k].q;
+            bt = all[k].tl;
+        }
+    }
+    // Past about 25 the candidates' batches cost more than the walkers' chains:
+    // 64 MiB of text, m = 10, d = 100k (cost 24.9) 436 us against 593 us for
+    // the better walker; m = 8, d = 10k (27.0) 900 us against 397 us.
+    if (best > 25.0)
+        return;
+    const uint32_t q = bq, t = 1u << bt;
+    // Entries: the first one of each gram at the gram's number (grams in
+    // order of word, then bit), the others behind them. Offsets descend so
+    // that a chain's starting positions ascend; longer strings first.
+    const uint32_t wb = 2 * q - 5, nw = 1u << wb, gmask = (1u << (2 * q)) - 1u;
+    auto place = [&](uint32_t g) { return (g & (nw - 1)) * 32 + (g >> wb); };
+    std::vector<uint32_t> order(ix->du);
+    for (uint32_t u = 0; u < ix->du; u++)
+        order[u] = u;
+    if (ix->var)
+        std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return S.len(a) > S.len(b); });
+    std::vector<uint32_t> bits(nw, 0);
+    for (uint32_t u = 0; u < ix->du; u++)
+        for (uint32_t off = 0; off < t; off++) {
+            const uint32_t k = place((uint32_t)(head[u] >> (2 * off)) & gmask);
+            bits[k >> 5] |= 1u << (k & 31);
+        }
+    std::vector<uint2> words(nw);
+    uint32_t ngrams = 0;
+    for (uint32_t w = 0; w < nw; w++) {
+        words[w] = make_uint2(bits[w], ngrams);
+        ngrams += (uint32_t)__builtin_popcount(bits[w]);
+    }
+    std::vector<GramEnt> ents(ngrams, GramEnt{0, 0, 0, NONE});
+    ents.reserve((uint64_t)ix->du * t);
+    std::vector<uint32_t> tail(ngrams, NONE);
+    for (uint32_t k = 0; k < t; k++) {
+        const uint32_t off = t - 1 - k;
+        for (uint32_t u : order) {
+            const uint32_t pl = place((uint32_t)(head[u] >> (2 * off)) & gmask);
+            const uint2 w = words[pl >> 5];
+            const uint32_t g = w.y + (uint32_t)__builtin_popcount(w.x & ((1u << (pl & 31)) - 1u));
+            const uint32_t kl = std::min<uint32_t>(16, S.len(u));
+            GramEnt e;
+            e.key = (uint32_t)head[u];
+            e.mask = kl == 16 ? NONE : (1u << (2 * kl)) - 1u;
+            e.meta = u << 4 | off;
+            e.next = NONE;
+            if (tail[g] == NONE) {
+                ents[g] = e;
+                tail[g] = g;
+            } else {
+                ents[tail[g]].next = (uint32_t)ents.size();
+                tail[g] = (uint32_t)ents.size();
+                ents.push_back(e);
+            }
+        }
+    }
+    std::vector<uint2> strs(ix->du);
+    std::vector<uint8_t> rows;
+    rows.reserve(ix->upats.size() + 16ull * ix->du);
+    for (uint32_t u = 0; u < ix->du; u++) {
+        strs[u] = make_uint2((uint32_t)(rows.size() / 16), S.len(u));
+        rows.insert(rows.end(), S.at(u), S.at(u) + S.len(u));
+        rows.resize((rows.size() + 15) / 16 * 16, 0);
+    }
+    ix->image.reserve(ix->image.size() + 4ull * (bits.size() + 2 * words.size() + 4 * ents.size() + 2 * strs.size()) +
+                      rows.size() + 2048);
+    G.q = q;
+    G.t_log = bt;
+    G.code_shift = sh;
+    G.bit_bytes = std::max<uint32_t>(16, nw * 4);
+    bits.resize(G.bit_bytes / 4, 0);
+    G.off_bits = append(ix->image, bits.data(), bits.size());
+    G.off_words = append(ix->image, words.data(), words.size());
+    G.off_ents = append(ix->image, ents.data(), ents.size());
+    G.off_strs = append(ix->image, strs.data(), strs.size());
+    G.off_rows = append(ix->image, rows.data(), rows.size());
+    ix->image.resize((ix->image.size() + 255) / 256 * 256, 0);
+    G.ok = 1;
+}
+
+}  // namespace mpm

@@ -646,6 +646,8 @@ mpm_status mpm_build_ac(const uint8_t *patterns, uint32_t d, uint32_t m, const m
         ix->d = d;
         dedup(patterns, d, m, ix);
         st = build_ac_tables(ix);
+        if (!st)
+            build_gram(ix);
         if (st) {
             delete ix;
             return st;
@@ -674,6 +676,8 @@ mpm_status mpm_build_wm(const uint8_t *patterns, uint32_t d, uint32_t m, const m
         ix->d = d;
         dedup(patterns, d, m, ix);
         st = build_wm_tables(ix, B);
+        if (!st)
+            build_gram(ix);
         if (st) {
             delete ix;
             return st;
@@ -734,6 +738,8 @@ mpm_status mpm_build_ac_var(const uint8_t *patterns, const uint64_t *offsets, ui
         st = dedup_var(patterns, offsets, d, ix);
         if (!st)
             st = build_ac_rev_tables(ix);
+        if (!st)
+            build_gram(ix);
         if (st) {
             delete ix;
             return st;
@@ -773,6 +779,8 @@ mpm_status mpm_build_wm_var(const uint8_t *patterns, const uint64_t *offsets, ui
                 memcpy(ix->wpats.data() + (uint64_t)u * lo, ix->upats.data() + ix->upoff[u], lo);
             st = build_wm_tables(ix, B);
         }
+        if (!st)
+            build_gram(ix);
         if (st) {
             delete ix;
             return st;
@@ -912,7 +920,11 @@ mpm_status workspace_sizes(const mpm_index *idx, uint64_t n, const mpm_variant *
     const uint64_t nt = (n_starts(n, idx->m) + tb - 1) / tb;
     *min_bytes = WS_HEADER_BYTES + 8 * nt;
     *full_bytes = *min_bytes;
-    if (full_bytes != min_bytes && nt && !cfg.dense) {  // dense output stages nothing
+    GramCfg g;
+    if (full_bytes != min_bytes && nt && gram_takes(idx, v) && gram_config(idx, v, n, &g)) {
+        // the filter scan keeps its occurrences in LDS
+        *full_bytes = std::max(*min_bytes, WS_HEADER_BYTES + 8 * g.nchunks);
+    } else if (full_bytes != min_bytes && nt && !cfg.dense) {  // dense output stages nothing
         st = resolve_variant(idx, v, nt, &cfg);
         if (st)
             return st;
@@ -970,11 +982,18 @@ mpm_status scan_with_workspace(const mpm_index *idx, const uint8_t *d_text, uint
                     (unsigned long long)work_bytes, (unsigned long long)(WS_HEADER_BYTES + 8 * nt));
     if (nt == 0)
         return launch_zero_totals(nullptr, 0, d_total, stream);
+    ScanDev sd;
+    memset(&sd, 0, sizeof sd);
+    sd.single = TextDesc{d_text, n, d_out, capacity, d_total, 0, nt};
+    sd.ntexts = 1;
+    sd.hdr = (uint32_t *)d_work;
+    sd.status = (uint64_t *)((uint8_t *)d_work + WS_HEADER_BYTES);
+    GramCfg g;
+    if (gram_takes(idx, v) && gram_config(idx, v, n, &g) && work_bytes >= WS_HEADER_BYTES + 8 * g.nchunks)
+        return gram_launch(idx, g, sd, stream);
     st = resolve_variant(idx, v, nt, &cfg, true);
     if (st)
         return st;
-    ScanDev sd;
-    memset(&sd, 0, sizeof sd);
     // staging: as many slots per virtual lane as the workspace holds, at most
     // one per starting position of the lane
     // (none for dense output, or for a counting call with no output at all)
@@ -993,13 +1012,8 @@ mpm_status scan_with_workspace(const mpm_index *idx, const uint8_t *d_text, uint
         sd.csr_uoff_lds = cfg.csr_lds;
         sd.csr_uids_lds = cfg.csr_lds + 4 * sd.csr_uoff_words;
     }
-    sd.single = TextDesc{d_text, n, d_out, capacity, d_total, 0, nt};
-    sd.multi = nullptr;
-    sd.ntexts = 1;
     sd.lane_bytes = cfg.lane_bytes;
     sd.ntiles = nt;
-    sd.hdr = (uint32_t *)d_work;
-    sd.status = (uint64_t *)((uint8_t *)d_work + WS_HEADER_BYTES);
     sd.mark_lds = cfg.mark_lds;
     return launch_scan(idx, cfg, sd, stream);
 }

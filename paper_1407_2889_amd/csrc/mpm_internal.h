@@ -2,6 +2,7 @@
 // scan kernels (mpm_scan.hip). Not part of the public interface.
 #pragma once
 
+#include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include <string>
@@ -102,6 +103,36 @@ struct WmDev {
     // longer strings first. Null for one length.
     const uint32_t *upoff;
     uint32_t var;
+};
+
+// q-gram filter tables (mpm_gram.cpp), kept for either index kind when the
+// set is sparse enough. Characters map to 2-bit codes (c >> code_shift) & 3,
+// k characters to sum_j code(c_j) << 2j. Sampled text positions are the
+// multiples of t = 1 << t_log; a sample is a candidate when the q-gram that
+// starts there occurs in a string at one of the offsets 0 .. t - 1, which
+// `bits` records (word = low 2q - 5 bits of the gram, bit = its upper five).
+// Every occurrence covers a whole sampled q-gram at such an offset, because
+// t + q - 1 <= m.
+struct GramEnt {      // one (string, offset) of a gram
+    uint32_t key;     // codes of the string's first characters (at most 16)
+    uint32_t mask;    // the bits of key that count
+    uint32_t meta;    // string << 4 | offset
+    uint32_t next;    // next entry of the same gram (all ones: none)
+};
+struct GramDev {
+    const uint32_t *bits;     // 4^q bits, copied to LDS
+    const uint2 *words;       // per word of bits: (the word, grams before it)
+    const GramEnt *ents;      // the first entry of gram number k at k, the others after them;
+                              // a chain's offsets descend, longer strings first
+    const uint2 *strs;        // per string: first 16-byte row, length
+    const uint8_t *rows;      // the strings, each padded to whole 16-byte rows
+    const uint32_t *uoff;
+    const uint32_t *uids;
+    uint32_t q, t_log, code_shift;
+    uint32_t bit_bytes;       // bytes of bits (multiple of 16)
+    uint32_t m;               // shortest string
+    uint32_t n_single;
+    IdGroups grp;
 };
 
 // One text of a launch. Tiles of a launch are numbered globally; a text
@@ -248,6 +279,12 @@ struct mpm_index {
     uint64_t off_go = 0, go_bytes = 0, sup_off = 0;
     uint64_t table_bytes = 0;
     const uint8_t *d_image = nullptr;
+
+    // q-gram filter (mpm_gram.cpp); ok = 0: the set has none
+    struct Gram {
+        uint32_t ok = 0, q = 0, t_log = 0, code_shift = 0, bit_bytes = 0;
+        uint64_t off_bits = 0, off_words = 0, off_ents = 0, off_strs = 0, off_rows = 0;
+    } gram;
 };
 
 namespace mpm {
@@ -296,6 +333,28 @@ mpm_status var_launch(const mpm_index *ix, const LaunchCfg &c, const ScanDev &sd
 // Text-access ladder variants (mpm_scan_ladder.hip).
 const void *ladder_kernel(const mpm_index *ix, const LaunchCfg &c);
 mpm_status ladder_launch(const mpm_index *ix, const LaunchCfg &c, const ScanDev &sd, void *stream);
+// q-gram filter scans (mpm_gram.cpp, mpm_scan_gram.hip).
+struct GramCfg {
+    uint32_t W;            // threads per workgroup
+    uint32_t blocks;       // 4 KiB text blocks per wave and chunk
+    uint32_t grid;
+    uint32_t lds_bytes;
+    uint32_t wave_bytes;   // LDS bytes of one wave's buffers
+    uint32_t hits;         // occurrences a wave keeps in LDS
+    uint64_t nchunks;
+};
+void build_gram(mpm_index *ix);
+struct DeviceLimits {
+    int cus = 0;
+    int max_lds = 0;
+};
+DeviceLimits limits();
+IdGroups id_groups(const mpm_index *ix);
+// The id CSR in an uploaded index's device image.
+void id_csr(const mpm_index *ix, const uint32_t **uoff, const uint32_t **uids);
+bool gram_takes(const mpm_index *ix, const mpm_variant *v);
+bool gram_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, GramCfg *g);
+mpm_status gram_launch(const mpm_index *ix, const GramCfg &g, const ScanDev &sd, void *stream);
 uint32_t batch_kind(const mpm_index *ix, const LaunchCfg &c);
 // Batched launches run one kernel per walker kind (BK_*, with BK_SWAR).
 uint32_t batch_grid(uint32_t kind, uint32_t W, uint32_t lds_bytes, uint64_t ntiles,

@@ -53,12 +53,7 @@ __global__ void zero_totals_kernel(uint64_t *const *ptrs, uint32_t count, uint64
         *ptrs[i] = 0;
 }
 
-struct DeviceLimits {
-    int cus = 0;
-    int max_lds = 0;
-};
-
-static DeviceLimits limits()
+DeviceLimits limits()
 {
     static std::mutex mu;
     static DeviceLimits cache[64];
@@ -82,7 +77,7 @@ static DeviceLimits limits()
     return cache[dev];
 }
 
-static IdGroups id_groups(const mpm_index *ix)
+IdGroups id_groups(const mpm_index *ix)
 {
     IdGroups g;
     memset(&g, 0, sizeof g);
@@ -94,6 +89,13 @@ static IdGroups id_groups(const mpm_index *ix)
     }
     g.u0[g.n] = g.n < ix->grp_u0.size() ? ix->grp_u0[g.n] : ix->du;
     return g;
+}
+
+void id_csr(const mpm_index *ix, const uint32_t **uoff, const uint32_t **uids)
+{
+    const bool ac = ix->algo == MPM_ALGO_AC;
+    *uoff = (const uint32_t *)(ix->d_image + (ac ? ix->off_c : ix->off_f));
+    *uids = (const uint32_t *)(ix->d_image + (ac ? ix->off_d : ix->off_g));
 }
 
 AcDev ac_dev(const mpm_index *ix, uint32_t reserve)
