@@ -241,6 +241,13 @@ void build_gram(mpm_index *ix)
     ix->image.reserve(ix->image.size() + 4ull * (bits.size() + 2 * words.size() + 4 * ents.size() + 2 * strs.size()) +
                       rows.size() + 2048);
     G.q = q;
+    G.hit = 1e-9;
+    for (uint32_t u = 0; u < ix->du; u++) {
+        double pr = 1;
+        for (uint32_t j = 0; j < std::min<uint32_t>(S.len(u), 25); j++)
+            pr *= share[(head[u] >> (2 * j)) & 3u];
+        G.hit += pr;
+    }
     G.t_log = bt;
     G.code_shift = sh;
     G.bit_bytes = std::max<uint32_t>(16, nw * 4);

@@ -920,10 +920,10 @@ mpm_status workspace_sizes(const mpm_index *idx, uint64_t n, const mpm_variant *
     const uint64_t nt = (n_starts(n, idx->m) + tb - 1) / tb;
     *min_bytes = WS_HEADER_BYTES + 8 * nt;
     *full_bytes = *min_bytes;
-    GramCfg g;
-    if (full_bytes != min_bytes && nt && gram_takes(idx, v) && gram_config(idx, v, n, &g)) {
-        // the filter scan keeps its occurrences in LDS
-        *full_bytes = std::max(*min_bytes, WS_HEADER_BYTES + 8 * g.nchunks);
+    if (full_bytes != min_bytes && nt && gram_takes(idx, v, n)) {
+        // the filter scan keeps its occurrences in LDS; room for the finest
+        // cut it makes of any text up to n bytes
+        *full_bytes = std::max(*min_bytes, WS_HEADER_BYTES + 8 * (n / GRAM_CHUNK_MIN + 2));
     } else if (full_bytes != min_bytes && nt && !cfg.dense) {  // dense output stages nothing
         st = resolve_variant(idx, v, nt, &cfg);
         if (st)
@@ -989,7 +989,8 @@ mpm_status scan_with_workspace(const mpm_index *idx, const uint8_t *d_text, uint
     sd.hdr = (uint32_t *)d_work;
     sd.status = (uint64_t *)((uint8_t *)d_work + WS_HEADER_BYTES);
     GramCfg g;
-    if (gram_takes(idx, v) && gram_config(idx, v, n, &g) && work_bytes >= WS_HEADER_BYTES + 8 * g.nchunks)
+    if (gram_takes(idx, v, n) && gram_config(idx, v, n, (uint32_t)((uintptr_t)d_text & 15), &g) &&
+        work_bytes >= WS_HEADER_BYTES + 8 * g.nchunks)
         return gram_launch(idx, g, sd, stream);
     st = resolve_variant(idx, v, nt, &cfg, true);
     if (st)

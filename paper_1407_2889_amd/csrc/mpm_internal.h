@@ -283,6 +283,7 @@ struct mpm_index {
     // q-gram filter (mpm_gram.cpp); ok = 0: the set has none
     struct Gram {
         uint32_t ok = 0, q = 0, t_log = 0, code_shift = 0, bit_bytes = 0;
+        double hit = 0;  // expected occurrences per text byte
         uint64_t off_bits = 0, off_words = 0, off_ents = 0, off_strs = 0, off_rows = 0;
     } gram;
 };
@@ -336,13 +337,15 @@ mpm_status ladder_launch(const mpm_index *ix, const LaunchCfg &c, const ScanDev 
 // q-gram filter scans (mpm_gram.cpp, mpm_scan_gram.hip).
 struct GramCfg {
     uint32_t W;            // threads per workgroup
-    uint32_t blocks;       // 4 KiB text blocks per wave and chunk
+    uint32_t blocks;       // text blocks per wave and chunk
     uint32_t grid;
     uint32_t lds_bytes;
     uint32_t wave_bytes;   // LDS bytes of one wave's buffers
     uint32_t hits;         // occurrences a wave keeps in LDS
+    uint64_t nblocks;      // blocks of the text
     uint64_t nchunks;
 };
+static const uint64_t GRAM_CHUNK_MIN = 16384;  // text bytes of the smallest chunk
 void build_gram(mpm_index *ix);
 struct DeviceLimits {
     int cus = 0;
@@ -352,8 +355,8 @@ DeviceLimits limits();
 IdGroups id_groups(const mpm_index *ix);
 // The id CSR in an uploaded index's device image.
 void id_csr(const mpm_index *ix, const uint32_t **uoff, const uint32_t **uids);
-bool gram_takes(const mpm_index *ix, const mpm_variant *v);
-bool gram_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, GramCfg *g);
+bool gram_takes(const mpm_index *ix, const mpm_variant *v, uint64_t n);
+bool gram_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, uint32_t lo, GramCfg *g);
 mpm_status gram_launch(const mpm_index *ix, const GramCfg &g, const ScanDev &sd, void *stream);
 uint32_t batch_kind(const mpm_index *ix, const LaunchCfg &c);
 // Batched launches run one kernel per walker kind (BK_*, with BK_SWAR).

@@ -8,7 +8,8 @@
 //
 //   1. A wave takes 4 KiB of text, 64 contiguous bytes per lane (four 16-byte
 //      loads back to back, the next block's in flight), and packs them to
-//      2-bit codes: four registers per lane, also written to LDS.
+//      2-bit codes: four registers per lane. (128 bytes per lane measured 10 %
+//      slower, 24 waves per CU instead of 16 as well.)
 //   2. One LDS bit per sample (every t-th position) tells whether the q-gram
 //      there occurs in a string at an offset below t: a shift, a mask, a
 //      ds_read, two shifts, one v_alignbit to collect the bit.
@@ -27,9 +28,9 @@
 //
 // Measured (EST-shaped text, walkers before, filter after, us): 256 MiB,
 // d = 1000, m = 16: AC 102 -> 67, WM 100 -> 67 (4.0 TB/s of text); 128 MiB,
-// d = 10k, m = 16, AC 369 -> 52; 64 MiB, d = 100k, m = 16, WM 3572 -> 108;
-// 64 MiB, d = 1000, m = 8 with counts, WM 420 -> 135; 128 MiB, lengths 8-32,
-// AC 134 -> 73; 32 MiB, lengths 8-32, WM 2150 -> 31.
+// d = 10k, m = 16, AC 366 -> 48; 64 MiB, d = 100k, m = 16, WM 3577 -> 109;
+// 64 MiB, d = 1000, m = 8 with counts, WM 422 -> 99; 128 MiB, lengths 8-32,
+// AC 135 -> 69; 32 MiB, lengths 8-32, WM 2132 -> 30.
 #include "mpm_gram.h"
 
 namespace mpm {
@@ -37,14 +38,25 @@ namespace mpm {
 namespace {
 
 constexpr uint32_t GBITS_OFF = LDS_CLS_OFF;         // filter bits, after the header
-// One wave's LDS: code words [3] = the 16 characters before the block,
-// [4 .. 260) the block, [260] the 16 after it; 64 candidate slots; 64 items;
-// then the occurrence list.
-constexpr uint32_t WV_CODES = 0;
-constexpr uint32_t WV_SLOTS = 264 * 4;
-constexpr uint32_t WV_ITEMS = WV_SLOTS + 64 * 4;
+constexpr uint32_t BIAS = 16;                       // items hold start + BIAS
+
+// One wave's LDS: code words ([3] the 16 characters before the block, from
+// [4] on the block, then the 16 after it), 64 items (first a batch's
+// candidates, then its strings to compare), and the occurrence list.
+constexpr int GN = 4;                               // 16-byte pieces per lane and block
+constexpr uint32_t GBLOCK = 1024 * GN;              // text bytes per wave and step
+static_assert(256 / 64 * GBLOCK >= GRAM_CHUNK_MIN, "workspace bound");
+constexpr uint32_t WV_ITEMS = (64 * GN + 8) * 4;
 constexpr uint32_t WV_HITS = WV_ITEMS + 64 * 8;
-constexpr uint32_t BIAS = 16;                       // items hold start - block + BIAS
+
+// The same value, hidden from the optimizer: addresses derived from it are
+// computed where they are used and not kept in registers across the passes
+// over a wave's text (91 instead of 128 registers).
+__device__ __forceinline__ uint64_t hidden(uint64_t x)
+{
+    asm volatile("" : "+s"(x));
+    return x;
+}
 
 // Write the pairs of up to 64 occurrences (one per active lane, in lane
 // order) from output slot o on; o moves past them.
@@ -69,7 +81,8 @@ __device__ __forceinline__ void write_hits(mpm_match *out_, uint64_t cap, uint64
 template <int TL, bool Var>
 struct GramScan {
     static constexpr uint32_t T = 1u << TL;
-    static constexpr uint32_t NS = 64u >> TL;  // samples per lane and block
+    static constexpr uint32_t NS = (16u * GN) >> TL;  // samples per lane and block
+    static constexpr uint32_t NM = (NS + 31) / 32;          // words of sample bits
     GramDev a;
     View text;
     IdMap im;
@@ -77,24 +90,26 @@ struct GramScan {
     uint32_t hcap;
     uint32_t amask, bsh, wmask;
 
-    // Whether the len bytes at view position s are string (row, len).
+    // Whether the len >= 4 bytes at view position s are string (row, len):
+    // whole 16-, 8- or 4-byte pieces, the last one ending with the string.
     __device__ __forceinline__ bool equal(uint64_t s, uint32_t row, uint32_t len) const
     {
-        glb_cptr<v4u> pat = (glb_cptr<v4u>)a.rows + row;
-        for (uint32_t j = 0; j < len; j += 16) {
-            const uint32_t rem = len - j;
-            const v4u t = text.piece(s + j);
-            const v4u d = t ^ pat[j >> 4];
-            uint32_t diff = 0;
-#pragma unroll
-            for (uint32_t k = 0; k < 4; ++k) {
-                const uint32_t n = rem > 4 * k ? rem - 4 * k : 0;  // bytes of this word that count
-                diff |= n >= 4 ? d[k] : d[k] & ((1u << (8 * n)) - 1u);
-            }
-            if (diff)
-                return false;
+        glb_cptr<uint8_t> t = text.p + s, q = (glb_cptr<uint8_t>)a.rows + (uint64_t)row * 16;
+        if (len < 16) {
+            if (len < 8)
+                return *(const GLB_AS u32_any *)t == *(const GLB_AS u32_any *)q &&
+                       *(const GLB_AS u32_any *)(t + len - 4) == *(const GLB_AS u32_any *)(q + len - 4);
+            return *(const GLB_AS u64_any *)t == *(const GLB_AS u64_any *)q &&
+                   *(const GLB_AS u64_any *)(t + len - 8) == *(const GLB_AS u64_any *)(q + len - 8);
         }
-        return true;
+        for (uint32_t j = 0;; j += 16) {
+            j = min(j, len - 16);
+            const v4u d = *(const GLB_AS v4u_any *)(t + j) ^ *(const GLB_AS v4u_any *)(q + j);
+            if (d.x | d.y | d.z | d.w)
+                return false;
+            if (j == len - 16)
+                return true;
+        }
     }
 
     // Codes of the 16 characters from `off` before the sample on.
@@ -138,48 +153,63 @@ struct GramScan {
                                         mpm_match *out, uint64_t cap, uint64_t &o) const
     {
         const uint32_t lane = threadIdx.x & 63u;
-        LDS_AS uint32_t *cw = lds_at<uint32_t>(wv + WV_CODES);
-        LDS_AS uint32_t *slot = lds_at<uint32_t>(wv + WV_SLOTS);
-        LDS_AS v2u *item = lds_at<v2u>(wv + WV_ITEMS);
+        LDS_AS uint32_t *cw = lds_at<uint32_t>(wv);
+        LDS_AS uint32_t *slot = lds_at<uint32_t>(wv + WV_ITEMS);
         nh = 0;
         nid = 0;
         if (b0 >= b1)
             return;
+        const uint64_t base = b0 * GBLOCK;
         uint32_t last = 0xffffffffu;  // Var: start of the last occurrence
-        Raw x;
-        load_block(text, b0, lane, x);
-        uint32_t prev = b0 ? codes16(text.piece(b0 * GBLOCK - 16), a.code_shift) : 0u;
+        v4u r[GN];
+        uint32_t c[GN + 1], cn[GN];  // codes of the current block (and 16 more), of the next
+        text.load(base, lane, r);
+        uint32_t prev = b0 ? codes16(text.piece(base - 16), a.code_shift) : 0u;
+        const uint32_t after = text.fix(codes16(text.piece(b1 * GBLOCK), a.code_shift), b1 * GBLOCK);
+        text.codes(base, lane, r, a.code_shift, cn);
+        if (b0 + 1 < b1)
+            text.load(base + GBLOCK, lane, r);
         for (uint64_t b = b0; b < b1; ++b) {
-            uint32_t c[5];
+            uint32_t ct = after;
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                c[k] = codes16(x.r[k], a.code_shift);
-            const uint32_t ct = codes16(x.tail, a.code_shift);
-            if (b + 1 < b1)
-                load_block(text, b + 1, lane, x);
-            *(LDS_AS v4u *)(cw + 4 + 4 * lane) = v4u{c[0], c[1], c[2], c[3]};
-            if (lane == 0) {
-                cw[3] = prev;
-                cw[260] = ct;
+            for (int k = 0; k < GN; ++k)
+                c[k] = cn[k];
+            if (b + 1 < b1) {
+                text.codes((b + 1) * GBLOCK, lane, r, a.code_shift, cn);
+                ct = (uint32_t)__builtin_amdgcn_readfirstlane((int)cn[0]);
+                if (b + 2 < b1)
+                    text.load((b + 2) * GBLOCK, lane, r);
             }
-            wave_sync();
-            c[4] = cw[8 + 4 * lane];
-            prev = (uint32_t)__builtin_amdgcn_readlane((int)c[3], 63);
-
+            c[GN] = from_next(c[0], ct);
             // one bit per sample, the first sample in the lowest bit
-            uint32_t mk[2] = {0, 0};
+            uint32_t mk[NM];
+            uint32_t cnt = 0;
+#pragma unroll
+            for (uint32_t h = 0; h < NM; ++h)
+                mk[h] = 0;
 #pragma unroll
             for (uint32_t s = 0; s < NS; ++s) {
                 const uint32_t k = (s * T) >> 4, sub = 2 * ((s * T) & 15);
                 const uint32_t y = sub ? __builtin_amdgcn_alignbit(c[k + 1], c[k], sub - 2) : c[k] << 2;
-                const uint32_t w = *(lds_cptr<uint32_t>)lds_at<const uint8_t>(GBITS_OFF + (y & amask));
-                mk[s >> 5] = __builtin_amdgcn_alignbit(w >> ((y >> bsh) & 31u), mk[s >> 5], 1);
+                const uint32_t x = *(lds_cptr<uint32_t>)lds_at<const uint8_t>(GBITS_OFF + (y & amask));
+                mk[s >> 5] = __builtin_amdgcn_alignbit(x >> ((y >> bsh) & 31u), mk[s >> 5], 1);
             }
             if (NS < 32)
                 mk[0] >>= (32 - NS) & 31;
-            const uint32_t cnt = __popc(mk[0]) + (NS > 32 ? __popc(mk[1]) : 0);
+#pragma unroll
+            for (uint32_t h = 0; h < NM; ++h)
+                cnt += __popc(mk[h]);
+            const uint32_t before = prev;
+            prev = (uint32_t)__builtin_amdgcn_readlane((int)c[GN - 1], 63);
             if (__ballot(cnt != 0) == 0)
                 continue;
+#pragma unroll
+            for (int k = 0; k < GN; k += 4)
+                *(LDS_AS v4u *)(cw + 4 + GN * lane + k) = v4u{c[k], c[k + 1], c[k + 2], c[k + 3]};
+            if (lane == 0) {
+                cw[3] = before;
+                cw[4 + 64 * GN] = ct;
+            }
             uint32_t tot;
             const uint32_t pre = wave_excl_sum(cnt, tot);
 #pragma unroll 1
@@ -187,28 +217,33 @@ struct GramScan {
                 wave_sync();
                 uint32_t rk = pre - win;  // below 64: this window's slot
 #pragma unroll
-                for (uint32_t h = 0; h < (NS > 32 ? 2u : 1u); ++h)
+                for (uint32_t h = 0; h < NM; ++h)
                     for (uint32_t mm = mk[h]; mm; mm &= mm - 1, ++rk)
                         if (rk < 64)
                             slot[rk] = lane * NS + 32 * h + (uint32_t)__builtin_ctz(mm);
                 wave_sync();
-                candidates(direct, b, slot, cw, item, min(64u, tot - win), nh, nid, last, out, cap, o);
+                const bool active = lane < tot - win;
+                uint32_t p = 0, code = 0, pv = 0;
+                if (active) {
+                    p = slot[lane] << TL;  // sample, relative to the block
+                    const uint32_t wi = p >> 4, sub = 2 * (p & 15);
+                    const uint32_t A = cw[3 + wi], B = cw[4 + wi], C = cw[5 + wi];
+                    code = __builtin_amdgcn_alignbit(C, B, sub);
+                    pv = __builtin_amdgcn_alignbit(B, A, sub);
+                }
+                candidates(direct, b * GBLOCK, active, p, code, pv, nh, nid, last, out, cap, o);
             }
         }
     }
 
-    __device__ __forceinline__ void candidates(bool direct, uint64_t b, LDS_AS uint32_t *slot, LDS_AS uint32_t *cw,
-                                               LDS_AS v2u *item, uint32_t n, uint32_t &nh, uint32_t &nid,
-                                               uint32_t &last, mpm_match *out, uint64_t cap, uint64_t &o) const
+    // One batch of candidates, one per active lane in text order.
+    __device__ __forceinline__ void candidates(bool direct, uint64_t base, bool active, uint32_t p, uint32_t code,
+                                               uint32_t pv, uint32_t &nh, uint32_t &nid, uint32_t &last,
+                                               mpm_match *out, uint64_t cap, uint64_t &o) const
     {
         const uint32_t lane = threadIdx.x & 63u;
-        uint32_t head = 0xffffffffu, code = 0, pv = 0, p = 0;
-        if (lane < n) {
-            p = slot[lane] << TL;  // sample, relative to the block
-            const uint32_t wi = p >> 4, sub = 2 * (p & 15);
-            const uint32_t A = cw[3 + wi], B = cw[4 + wi], C = cw[5 + wi];
-            code = __builtin_amdgcn_alignbit(C, B, sub);
-            pv = __builtin_amdgcn_alignbit(B, A, sub);
+        uint32_t head = 0xffffffffu;
+        if (active) {
             const uint2 w = a.words[code & wmask];
             head = w.y + __popc(w.x & ((1u << ((code >> (bsh - 2)) & 31u)) - 1u));
         }
@@ -225,8 +260,8 @@ struct GramScan {
         }
         if (__ballot(nm != 0) == 0)
             return;
-        const uint64_t vb = b * GBLOCK;
         const bool single = __ballot(nm > 1) == 0;
+        LDS_AS v2u *item = lds_at<v2u>(wv + WV_ITEMS);
         uint32_t tot = 0, pre = 0;
         if (!single)
             pre = wave_excl_sum(nm, tot);
@@ -253,7 +288,7 @@ struct GramScan {
                 act = lane < min(64u, tot - iw);
                 it = item[lane];
             }
-            check(direct, act, vb + it.x - BIAS, it.y, nh, nid, last, out, cap, o);
+            check(direct, act, base + it.x - BIAS, it.y, nh, nid, last, out, cap, o);
             iw += 64;
         } while (iw < tot);
     }
@@ -288,10 +323,12 @@ __global__ __launch_bounds__(W) void gram_kernel(GramDev a, ScanDev sd, uint32_t
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t lane = threadIdx.x & 63u;
 
+    if (threadIdx.x == 0) {
+        s_tile = take_ticket(hdr);
+        s_epoch = __hip_atomic_load(&hdr[WS_EPOCH], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     copy_to_lds<W>(GBITS_OFF, (const uint8_t *)a.bits, a.bit_bytes);
     load_groups(a.grp);
-    if (threadIdx.x == 0)
-        s_epoch = __hip_atomic_load(&hdr[WS_EPOCH], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
     GramScan<TL, Var> sc;
     sc.a = a;
@@ -314,25 +351,24 @@ __global__ __launch_bounds__(W) void gram_kernel(GramDev a, ScanDev sd, uint32_t
     const uint64_t cap = sd.single.cap;
 
     while (true) {
-        if (threadIdx.x == 0)
-            s_tile = take_ticket(hdr);
         __syncthreads();
         const uint64_t g = uniform64(s_tile);
         if (g >= ntiles)
             break;
         const uint64_t b0 = min((g * NW + wave) * blocks, nblocks);
         const uint64_t b1 = min(b0 + blocks, nblocks);
-        uint32_t nh, nid[1];
-        uint64_t ob[1] = {0};
+        uint32_t nh, nid;
         uint64_t o = 0;
 #pragma unroll 1
         for (uint32_t pass = 0; pass < 2; ++pass) {
-            sc.run(pass != 0, b0, b1, nh, nid[0], sd.single.out, cap, o);
+            sc.run(pass != 0, hidden(b0), b1, nh, nid, sd.single.out, cap, o);
             if (pass)
                 break;
-            chunk_offsets<W, 1>(nid, ob, s_scan, sd.status, g, 0, g + 1 == ntiles, sd.single.total,
-                                s_epoch | GRAM_EPOCH, &hdr[WS_ERR]);
-            o = uniform64(ob[0]);  // the wave's first output slot
+#pragma unroll
+            for (int k = 32; k >= 1; k >>= 1)
+                nid += __shfl_xor(nid, k, 64);
+            o = wave_offset<W>(nid, s_scan, sd.status, g, ntiles, sd.single.total, s_epoch | GRAM_EPOCH,
+                               &hdr[WS_ERR]);
             if (nh == 0 || o >= cap)
                 break;
             if (nh <= hits) {
@@ -347,6 +383,15 @@ __global__ __launch_bounds__(W) void gram_kernel(GramDev a, ScanDev sd, uint32_t
                 break;
             }
         }
+        if (gridDim.x >= ntiles)  // one chunk per workgroup
+            break;
+        if (threadIdx.x == 0)
+            s_tile = take_ticket(hdr);
+    }
+    if (gridDim.x == ntiles && ntiles <= WIDE_CHUNKS) {
+        if (threadIdx.x == 0 && s_tile + 1 == ntiles)
+            finish_wide(hdr, s_epoch);
+        return;
     }
     finish_launch(hdr, s_epoch);
 }
@@ -375,28 +420,33 @@ const void *kernel_of(uint32_t W, uint32_t tl, bool var)
 }  // namespace
 
 // Whether automatic placement runs an index through the filter.
-bool gram_takes(const mpm_index *ix, const mpm_variant *v)
+bool gram_takes(const mpm_index *ix, const mpm_variant *v, uint64_t n)
 {
-    if (!ix->gram.ok)
+    if (!ix->gram.ok || n < 64)
         return false;
     return !v || (v->placement == MPM_PLACE_AUTO && !(v->flags & ~(uint32_t)MPM_VARIANT_DENSE));
 }
 
-// Launch shape for a text of n bytes; false when the filter cannot run it.
-bool gram_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, GramCfg *g)
+// Launch shape for a text of n bytes that starts lo bytes past a 16-byte
+// boundary; false when the filter cannot run it.
+bool gram_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, uint32_t lo, GramCfg *g)
 {
     const mpm_index::Gram &G = ix->gram;
     const DeviceLimits lim = limits();
-    const uint64_t nblocks = (n + 15 + GBLOCK - 1) / GBLOCK;
     // Workgroups of 1024 threads share one copy of the bits between 16 waves;
     // texts that would leave CUs without work are cut finer.
+    const uint64_t nblocks = (n + lo + GBLOCK - 1) / GBLOCK;
     const uint32_t W = nblocks >= 16ull * lim.cus ? 1024 : 256;
     const uint32_t nw = W / 64;
+    // the occurrence lists: all the LDS that is left to 16 waves (their
+    // registers admit no second workgroup), 256 occurrences per wave of a
+    // small workgroup
     const uint32_t room = (uint32_t)lim.max_lds - GBITS_OFF - G.bit_bytes;
-    // the occurrence lists: 256 per wave, fewer beside a 128 KiB table
-    uint32_t hits = 256;
-    while (hits > 16 && (WV_HITS + 8 * hits) * nw > (W == 1024 && G.bit_bytes <= 32768 ? room / 2 : room))
-        hits /= 2;
+    if (room / nw < WV_HITS + 16 * 8)
+        return false;
+    uint32_t hits = (room / nw - WV_HITS) / 8;
+    hits = std::min<uint32_t>(hits, W == 1024 ? 1024 : 256) & ~1u;
+    g->nblocks = nblocks;
     g->W = W;
     g->hits = hits;
     g->wave_bytes = WV_HITS + 8 * hits;
@@ -410,9 +460,11 @@ bool gram_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, GramCfg 
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k, (int)W, g->lds_bytes) != hipSuccess || nb <= 0)
         nb = 1;
     const uint64_t slots = (uint64_t)nb * lim.cus;
-    // one round of chunks when the text allows, at most 16 blocks per wave
+    // One round of chunks, as each round waits for its first text and its
+    // offsets, unless the expected occurrences would not fit the lists.
     uint64_t blocks = (nblocks + slots * nw - 1) / (slots * nw);
-    blocks = std::min<uint64_t>(std::max<uint64_t>(blocks, 1), 16);
+    const double fit = 0.6 * hits / (GBLOCK * G.hit);
+    blocks = std::max<uint64_t>(1, std::min<uint64_t>(blocks, fit > 4096 ? 4096 : (uint64_t)fit));
     g->blocks = (uint32_t)blocks;
     g->nchunks = (nblocks + blocks * nw - 1) / (blocks * nw);
     uint64_t grid = v && v->grid ? v->grid : slots;
@@ -442,7 +494,7 @@ mpm_status gram_launch(const mpm_index *ix, const GramCfg &g, const ScanDev &sd,
     ScanDev s = sd;
     s.ntiles = g.nchunks;
     uint32_t blocks = g.blocks, hits = g.hits, wave_bytes = g.wave_bytes;
-    uint64_t nblocks = (sd.single.n + 15 + GBLOCK - 1) / GBLOCK;
+    uint64_t nblocks = g.nblocks;
     void *args[] = {&a, &s, &blocks, &nblocks, &hits, &wave_bytes};
     const hipError_t e = hipLaunchKernel(kernel_of(g.W, G.t_log, ix->var != 0), dim3(g.grid), dim3(g.W),
                                          args, g.lds_bytes, (hipStream_t)stream);
