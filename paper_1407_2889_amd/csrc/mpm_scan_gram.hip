@@ -196,6 +196,14 @@ struct GramScan {
             }
             if (NS < 32)
                 mk[0] >>= (32 - NS) & 31;
+            const uint64_t v0 = b * GBLOCK + lane * (16 * GN);
+            if (!text.whole<GN>(b * GBLOCK)) {
+                // nothing starts past the end (where codes read as zeros)
+                const uint32_t left = (uint32_t)(text.hi > v0 ? min(text.hi - v0 + T - 1, (uint64_t)16 * GN) : 0) >> TL;
+#pragma unroll
+                for (uint32_t h = 0; h < NM; ++h)
+                    mk[h] &= left >= 32 * h + 32 ? ~0u : left > 32 * h ? (1u << (left - 32 * h)) - 1u : 0u;
+            }
 #pragma unroll
             for (uint32_t h = 0; h < NM; ++h)
                 cnt += __popc(mk[h]);
