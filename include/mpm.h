@@ -77,8 +77,9 @@ typedef struct {
 } mpm_opts;
 
 #define MPM_PLACE_AUTO 0    /* in single-text scans without a flag (or with
-                               MPM_VARIANT_DENSE alone): the q-gram filter, when the
-                               builder kept one (see mpm_scan); otherwise LDS when the
+                               MPM_VARIANT_DENSE alone): the q-gram filter or the
+                               direct-address table, when the builder kept one (see
+                               mpm_scan); otherwise LDS when the
                                tables fit beside the scan's own LDS use, else
                                MPM_PLACE_HOT when the index has a hot part, else global */
 #define MPM_PLACE_LDS 1     /* matching tables copied into LDS once per workgroup */
@@ -255,8 +256,9 @@ mpm_status mpm_workspace_bytes(const mpm_index *idx, uint64_t n, const mpm_varia
  * Sets whose strings rule out most of a text by a few characters (most sets
  * of 8 characters and more, either index kind) keep a q-gram filter in their
  * image, and MPM_PLACE_AUTO scans through it: every t-th position is looked
- * up in a bit table in LDS, and only text near a candidate is compared. The
- * filter cuts the text into chunks of its own, whatever lane_bytes and
+ * up in a bit table in LDS, and only text near a candidate is compared. Dense
+ * sets of 2 to 8 characters keep a direct-address table instead: a window's
+ * characters are the index of its ids. Both scans cut the text into chunks of their own, whatever lane_bytes and
  * block_threads say; a workspace smaller than mpm_workspace_bytes may make
  * the scan walk the tables instead. The list is the same.
  * Errors: EINVAL, ETOOBIG (n >= 2^32), ESTATE (index not uploaded), ENOMEM

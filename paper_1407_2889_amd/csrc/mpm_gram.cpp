@@ -25,6 +25,14 @@ const uint32_t Q_MAX = 10;        // 4^10 bits = 128 KiB of the 160 KiB LDS
 const uint32_t CHAIN_MAX = 64;    // entries of one gram
 const uint32_t NONE = 0xffffffffu;
 
+uint32_t gram_of(const uint8_t *p, uint32_t k, uint32_t sh)
+{
+    uint32_t h = 0;
+    for (uint32_t j = 0; j < k; j++)
+        h |= ((p[j] >> sh) & 3u) << (2 * j);
+    return h;
+}
+
 template <typename T>
 uint64_t append(std::vector<uint8_t> &img, const T *src, uint64_t count)
 {
@@ -241,6 +249,7 @@ void build_gram(mpm_index *ix)
     ix->image.reserve(ix->image.size() + 4ull * (bits.size() + 2 * words.size() + 4 * ents.size() + 2 * strs.size()) +
                       rows.size() + 2048);
     G.q = q;
+    G.cost = best;
     G.hit = 1e-9;
     for (uint32_t u = 0; u < ix->du; u++) {
         double pr = 1;
@@ -259,6 +268,100 @@ void build_gram(mpm_index *ix)
     G.off_rows = append(ix->image, rows.data(), rows.size());
     ix->image.resize((ix->image.size() + 255) / 256 * 256, 0);
     G.ok = 1;
+}
+
+// The direct-address tables of a set with 2 <= m <= 8; leaves direct.ok = 0
+// when the set does not fit them.
+void build_direct(mpm_index *ix)
+{
+    mpm_index::Direct &D = ix->direct;
+    const uint32_t m = ix->m;
+    if (ix->var || m < 2 || m > 8 || ix->du == 0 || ix->uids.size() >= (1u << 24))
+        return;
+    const uint32_t H = 1u << (2 * m);
+    double freq[256];
+    const uint32_t sh = code_shift_of(ix->upats, freq, nullptr);
+    uint8_t main4[4];
+    bool is_main[256] = {false};
+    for (uint32_t k = 0; k < 4; k++) {
+        int best = -1;
+        for (uint32_t b = 0; b < 256; b++)
+            if (((b >> sh) & 3u) == k && freq[b] > 0 && (best < 0 || freq[b] > freq[best]))
+                best = (int)b;
+        main4[k] = best < 0 ? (uint8_t)(((k + 1) & 3u) << sh) : (uint8_t)best;
+        if (best >= 0)
+            is_main[best] = true;
+    }
+    std::vector<uint32_t> string_of(H, NONE), odd;
+    for (uint32_t u = 0; u < ix->du; u++) {
+        const uint8_t *p = ix->upats.data() + (uint64_t)u * m;
+        bool all = true;
+        for (uint32_t j = 0; j < m; j++)
+            all &= is_main[p[j]];
+        if (!all)
+            odd.push_back(u);
+        else if (ix->uoff[u + 1] - ix->uoff[u] > 15)  // counts have four bits
+            return;
+        else
+            string_of[gram_of(p, m, sh)] = u;
+    }
+    if (odd.size() * 10 > ix->du)  // most windows would be compared byte by byte
+        return;
+    const uint32_t nw = std::max<uint32_t>(4, H / 8);
+    std::vector<uint32_t> table(2 * nw, 0), ids;
+    ids.reserve(ix->uids.size());
+    auto take = [&](uint32_t u) {
+        ids.insert(ids.end(), ix->uids.begin() + ix->uoff[u], ix->uids.begin() + ix->uoff[u + 1]);
+        return ix->uoff[u + 1] - ix->uoff[u];
+    };
+    for (uint32_t c = 0; c < H; c++) {
+        if ((c & 7) == 0)
+            table[nw + (c >> 3)] = (uint32_t)ids.size();
+        if (string_of[c] != NONE)
+            table[c >> 3] |= take(string_of[c]) << (4 * (c & 7));
+    }
+    D.code_shift = sh;
+    memcpy(&D.main4, main4, 4);
+    D.table_bytes = nw * 4;
+    if (!odd.empty()) {
+        std::vector<uint32_t> bits(std::max<uint32_t>(4, H / 32), 0);
+        for (uint32_t u : odd) {
+            const uint32_t c = gram_of(ix->upats.data() + (uint64_t)u * m, m, sh);
+            bits[c >> 5] |= 1u << (c & 31);
+        }
+        std::vector<uint2> words(bits.size());
+        uint32_t n = 0;
+        for (size_t w = 0; w < bits.size(); w++) {
+            words[w] = make_uint2(bits[w], n);
+            n += (uint32_t)__builtin_popcount(bits[w]);
+        }
+        std::vector<OddEnt> ents(n, OddEnt{0, 0, 0, NONE, 0});
+        std::vector<uint32_t> tail(n, NONE);
+        for (uint32_t u : odd) {
+            const uint8_t *p = ix->upats.data() + (uint64_t)u * m;
+            const uint32_t c = gram_of(p, m, sh);
+            const uint32_t k = words[c >> 5].y + (uint32_t)__builtin_popcount(bits[c >> 5] & ((1u << (c & 31)) - 1u));
+            OddEnt e = {0, (uint32_t)ids.size(), 0, NONE, 0};
+            e.count = take(u);
+            memcpy(&e.bytes, p, m);
+            if (tail[k] == NONE) {
+                ents[k] = e;
+                tail[k] = k;
+            } else {
+                ents[tail[k]].next = (uint32_t)ents.size();
+                tail[k] = (uint32_t)ents.size();
+                ents.push_back(e);
+            }
+        }
+        D.odd_bytes = (uint32_t)bits.size() * 4;
+        D.off_bits = append(ix->image, bits.data(), bits.size());
+        D.off_words = append(ix->image, words.data(), words.size());
+        D.off_ents = append(ix->image, ents.data(), ents.size());
+    }
+    D.off_table = append(ix->image, table.data(), table.size());
+    D.off_ids = append(ix->image, ids.data(), ids.size());
+    ix->image.resize((ix->image.size() + 255) / 256 * 256, 0);
+    D.ok = 1;
 }
 
 }  // namespace mpm

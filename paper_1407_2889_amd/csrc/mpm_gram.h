@@ -1,6 +1,6 @@
 // Device helpers of the scans that look at text positions known beforehand
-// (mpm_scan_gram.hip): a wave takes 4 KiB of text, 64 contiguous bytes per
-// lane, as 2-bit character codes.
+// (mpm_scan_gram.hip, mpm_scan_direct.hip): a wave takes 4 KiB of text, 64
+// contiguous bytes per lane, as 2-bit character codes.
 #pragma once
 #include "mpm_scan_impl.h"
 
@@ -108,6 +108,28 @@ struct View {
         }
     }
 };
+
+// The same value, hidden from the optimizer: addresses derived from it are
+// computed where they are used and not kept in registers across the passes
+// over a wave's text (91 instead of 128 registers).
+__device__ __forceinline__ uint64_t hidden(uint64_t x)
+{
+    asm volatile("" : "+s"(x));
+    return x;
+}
+
+// Inclusive prefix sum over the wave's lanes: four row shifts and two row
+// broadcasts, one add each.
+__device__ __forceinline__ uint32_t wave_incl_sum(uint32_t x)
+{
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true);   // row_shr:1
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, true);   // row_shr:2
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true);   // row_shr:4
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true);   // row_shr:8
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x142, 0xa, 0xf, false);  // row_bcast:15
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x143, 0xc, 0xf, false);  // row_bcast:31
+    return x;
+}
 
 // Lanes below this one set in bal.
 __device__ __forceinline__ uint32_t below(uint64_t bal)

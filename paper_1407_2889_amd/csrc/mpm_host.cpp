@@ -647,7 +647,7 @@ mpm_status mpm_build_ac(const uint8_t *patterns, uint32_t d, uint32_t m, const m
         dedup(patterns, d, m, ix);
         st = build_ac_tables(ix);
         if (!st)
-            build_gram(ix);
+            build_gram(ix), build_direct(ix);
         if (st) {
             delete ix;
             return st;
@@ -677,7 +677,7 @@ mpm_status mpm_build_wm(const uint8_t *patterns, uint32_t d, uint32_t m, const m
         dedup(patterns, d, m, ix);
         st = build_wm_tables(ix, B);
         if (!st)
-            build_gram(ix);
+            build_gram(ix), build_direct(ix);
         if (st) {
             delete ix;
             return st;
@@ -739,7 +739,7 @@ mpm_status mpm_build_ac_var(const uint8_t *patterns, const uint64_t *offsets, ui
         if (!st)
             st = build_ac_rev_tables(ix);
         if (!st)
-            build_gram(ix);
+            build_gram(ix), build_direct(ix);
         if (st) {
             delete ix;
             return st;
@@ -780,7 +780,7 @@ mpm_status mpm_build_wm_var(const uint8_t *patterns, const uint64_t *offsets, ui
             st = build_wm_tables(ix, B);
         }
         if (!st)
-            build_gram(ix);
+            build_gram(ix), build_direct(ix);
         if (st) {
             delete ix;
             return st;

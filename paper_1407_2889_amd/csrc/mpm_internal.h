@@ -135,6 +135,29 @@ struct GramDev {
     IdGroups grp;
 };
 
+// Direct-address tables of a set with 2 <= m <= 8 (mpm_gram.cpp), for the
+// strings made of each code's main byte: per window of m codes the number of
+// its ids (four bits, eight windows to a word), then per word the first id
+// slot of its windows; ids in window order. The other strings ("odd") have a
+// bit per window code (word = code >> 5) and a chain of 8-byte strings.
+struct OddEnt {
+    uint64_t bytes;   // the string, zero padded
+    uint32_t first;   // its ids: [first, first + count)
+    uint32_t count;
+    uint32_t next;    // next entry of the same code (all ones: none)
+    uint32_t pad;
+};
+struct DirectDev {
+    const uint32_t *table;      // counts, then slots: table_bytes each, copied to LDS
+    const uint32_t *odd_bits;   // 4^m bits, copied to LDS
+    const uint2 *odd_words;     // per word of odd_bits: (the word, codes before it)
+    const OddEnt *odd_ents;
+    const uint32_t *ids;
+    uint32_t table_bytes, odd_bytes;  // multiples of 16; odd_bytes 0: no odd strings
+    uint32_t m, code_shift;
+    uint32_t main4;             // main byte of code k in byte k (a byte of another code: none)
+};
+
 // One text of a launch. Tiles of a launch are numbered globally; a text
 // owns tiles [tile_begin, tile_begin + ntiles).
 struct TextDesc {
@@ -283,9 +306,15 @@ struct mpm_index {
     // q-gram filter (mpm_gram.cpp); ok = 0: the set has none
     struct Gram {
         uint32_t ok = 0, q = 0, t_log = 0, code_shift = 0, bit_bytes = 0;
+        double cost = 0; // expected vector instructions per text byte (mpm_gram.cpp)
         double hit = 0;  // expected occurrences per text byte
         uint64_t off_bits = 0, off_words = 0, off_ents = 0, off_strs = 0, off_rows = 0;
     } gram;
+    // direct-address table (mpm_gram.cpp); ok = 0: the set has none
+    struct Direct {
+        uint32_t ok = 0, code_shift = 0, main4 = 0, table_bytes = 0, odd_bytes = 0;
+        uint64_t off_table = 0, off_ids = 0, off_bits = 0, off_words = 0, off_ents = 0;
+    } direct;
 };
 
 namespace mpm {
@@ -344,9 +373,12 @@ struct GramCfg {
     uint32_t hits;         // occurrences a wave keeps in LDS
     uint64_t nblocks;      // blocks of the text
     uint64_t nchunks;
+    bool direct;           // the direct-address scan
+    uint32_t split;        // log2 of the waves that share a block (direct)
 };
-static const uint64_t GRAM_CHUNK_MIN = 16384;  // text bytes of the smallest chunk
+static const uint64_t GRAM_CHUNK_MIN = 4096;   // text bytes of the smallest chunk
 void build_gram(mpm_index *ix);
+void build_direct(mpm_index *ix);
 struct DeviceLimits {
     int cus = 0;
     int max_lds = 0;
@@ -358,6 +390,8 @@ void id_csr(const mpm_index *ix, const uint32_t **uoff, const uint32_t **uids);
 bool gram_takes(const mpm_index *ix, const mpm_variant *v, uint64_t n);
 bool gram_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, uint32_t lo, GramCfg *g);
 mpm_status gram_launch(const mpm_index *ix, const GramCfg &g, const ScanDev &sd, void *stream);
+bool direct_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, uint32_t lo, GramCfg *g);
+mpm_status direct_launch(const mpm_index *ix, const GramCfg &g, const ScanDev &sd, void *stream);
 uint32_t batch_kind(const mpm_index *ix, const LaunchCfg &c);
 // Batched launches run one kernel per walker kind (BK_*, with BK_SWAR).
 uint32_t batch_grid(uint32_t kind, uint32_t W, uint32_t lds_bytes, uint64_t ntiles,

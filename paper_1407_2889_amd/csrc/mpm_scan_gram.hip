@@ -49,15 +49,6 @@ static_assert(256 / 64 * GBLOCK >= GRAM_CHUNK_MIN, "workspace bound");
 constexpr uint32_t WV_ITEMS = (64 * GN + 8) * 4;
 constexpr uint32_t WV_HITS = WV_ITEMS + 64 * 8;
 
-// The same value, hidden from the optimizer: addresses derived from it are
-// computed where they are used and not kept in registers across the passes
-// over a wave's text (91 instead of 128 registers).
-__device__ __forceinline__ uint64_t hidden(uint64_t x)
-{
-    asm volatile("" : "+s"(x));
-    return x;
-}
-
 // Write the pairs of up to 64 occurrences (one per active lane, in lane
 // order) from output slot o on; o moves past them.
 __device__ __forceinline__ void write_hits(mpm_match *out_, uint64_t cap, uint64_t &o, bool active,
@@ -430,7 +421,7 @@ const void *kernel_of(uint32_t W, uint32_t tl, bool var)
 // Whether automatic placement runs an index through the filter.
 bool gram_takes(const mpm_index *ix, const mpm_variant *v, uint64_t n)
 {
-    if (!ix->gram.ok || n < 64)
+    if ((!ix->gram.ok && !ix->direct.ok) || n < 64)
         return false;
     return !v || (v->placement == MPM_PLACE_AUTO && !(v->flags & ~(uint32_t)MPM_VARIANT_DENSE));
 }
@@ -440,6 +431,12 @@ bool gram_takes(const mpm_index *ix, const mpm_variant *v, uint64_t n)
 bool gram_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, uint32_t lo, GramCfg *g)
 {
     const mpm_index::Gram &G = ix->gram;
+    // The direct-address scan costs the same whatever the candidates; past a
+    // filter cost of about 18 it is the faster one (64 MiB, m = 8: d = 5000,
+    // cost 16.7, filter 155 us, direct 186; d = 6000, 18.4, 201 and 189).
+    g->direct = !G.ok || (ix->direct.ok && G.cost > 18.0);
+    if (g->direct)
+        return direct_config(ix, v, n, lo, g);
     const DeviceLimits lim = limits();
     // Workgroups of 1024 threads share one copy of the bits between 16 waves;
     // texts that would leave CUs without work are cut finer.
@@ -483,6 +480,8 @@ bool gram_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, uint32_t
 
 mpm_status gram_launch(const mpm_index *ix, const GramCfg &g, const ScanDev &sd, void *stream)
 {
+    if (g.direct)
+        return direct_launch(ix, g, sd, stream);
     const mpm_index::Gram &G = ix->gram;
     GramDev a;
     const uint8_t *img = ix->d_image;

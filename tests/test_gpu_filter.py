@@ -96,6 +96,23 @@ def test_text_ends_and_alignments(mpm, m):
             check(run(mpm, ix, T, mis), want, f"m={m} n={n} mis={mis}")
 
 
+@pytest.mark.parametrize("m,d", [(2, 9), (3, 40), (5, 900), (7, 9000), (8, 9000), (8, 60_000)])
+def test_direct_address_sets(mpm, m, d):
+    """Sets dense enough for the direct-address table: texts of one wave, of
+    waves sharing a block (below 8 MiB), and of several blocks per wave; text
+    bytes N and newline that share a code with a base, strings that hold N."""
+    t = synth.est_text(9_000_000, seed=300 + m)
+    P = synth.pattern_set(t, d=d, m=m, n_planted=d // 4, seed=301 + m).patterns
+    if d > 100:
+        P[:20] = np.where(np.arange(m) == m // 2, ord("N"), P[:20])
+    ix = mpm.build_ac(P, upload=True)
+    for n, mis in ((len(t), 0), (4_200_001, 5), (1_000_003, 9), (70_001, 15), (300, 2)):
+        say(f"[direct] m={m} d={d} n={n} mis={mis}")
+        want = oracle.parallel_scan(oracle.Win(P), t[:n])
+        check(run(mpm, ix, t[:n], mis, mpm.variant(block_threads=1024, flags=mpm.VARIANT_DENSE)), want,
+              f"m={m} d={d} n={n}")
+
+
 def low_complexity():
     rng = np.random.default_rng(3)
     a16 = np.full((3, 16), 65, np.uint8)
