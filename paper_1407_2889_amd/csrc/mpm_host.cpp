@@ -7,6 +7,7 @@
 
 #include <algorithm>
 #include <map>
+#include <memory>
 #include <numeric>
 #include <tuple>
 #include <vector>
@@ -1078,6 +1079,9 @@ static uint32_t launch_key(uint32_t kind, const LaunchCfg &c)
     return (kind & 0xffu) << 16 | (c.block_threads & 0x3fffu) << 2 | lds_class;
 }
 
+// All requests of the q-gram filter share one launch.
+static const uint32_t GRAM_KEY = BK_GRAM << 16 | 1024u << 2;
+
 struct mpm_batch {
     // One persistent launch per block size; its texts ordered by index and
     // walker kind so that LDS tables are reused across consecutive chunks.
@@ -1091,6 +1095,10 @@ struct mpm_batch {
         std::vector<BatchIndex> idx;
         uint64_t ntiles = 0;
         uint64_t text_off = 0, idx_off = 0, work_off = 0, stage_off = 0;
+        // filter launch (BK_GRAM): ntiles counts its parts
+        std::vector<GramDev> gidx;
+        GramPieces cut;
+        uint64_t part_off = 0, piece_off = 0, ticket_off = 0;
     };
     std::vector<mpm_request> reqs;
     std::vector<Group> groups;
@@ -1109,12 +1117,33 @@ struct mpm_batch {
     hipEvent_t fork = nullptr;
 };
 
-extern "C" {
-
-mpm_status mpm_batch_plan(const mpm_request *reqs, uint32_t count, mpm_batch **out)
+// Warm-up, then `reps` launches between two events: the mean launch.
+template <class F>
+static mpm_status time_launches(F launch, hipStream_t s, uint32_t reps, float *ms_out)
 {
-    if (!out || (!reqs && count))
-        return fail(MPM_EINVAL, "mpm_batch_plan: null argument");
+    hipEvent_t a, z;
+    if (hipEventCreate(&a) != hipSuccess || hipEventCreate(&z) != hipSuccess)
+        return fail(MPM_EHIP, "mpm_tune_time: event creation failed");
+    mpm_status st = launch();
+    (void)hipEventRecord(a, s);
+    for (uint32_t r = 0; r < reps && st == MPM_OK; r++)
+        st = launch();
+    (void)hipEventRecord(z, s);
+    float ms = 0.f;
+    if (st == MPM_OK && hipEventSynchronize(z) == hipSuccess)
+        (void)hipEventElapsedTime(&ms, a, z);
+    (void)hipEventDestroy(a);
+    (void)hipEventDestroy(z);
+    if (st)
+        return st;
+    *ms_out = ms / (float)reps;
+    return MPM_OK;
+}
+
+// sizing: a plan for its device bytes alone (no buffers yet, index not
+// uploaded).
+static mpm_status plan_batch(const mpm_request *reqs, uint32_t count, bool sizing, mpm_batch **out)
+{
     *out = nullptr;
     try {
         mpm_batch *b = new mpm_batch();
@@ -1130,11 +1159,11 @@ mpm_status mpm_batch_plan(const mpm_request *reqs, uint32_t count, mpm_batch **o
         std::map<uint32_t, std::vector<Item>> byw;
         for (uint32_t k = 0; k < count; k++) {
             const mpm_request &r = reqs[k];
-            if (!r.idx || !r.d_total || (r.n && !r.d_text) || (r.capacity && !r.d_out)) {
+            if (!sizing && (!r.idx || !r.d_total || (r.n && !r.d_text) || (r.capacity && !r.d_out))) {
                 delete b;
                 return fail(MPM_EINVAL, "mpm_batch_plan: request %u has a null pointer", k);
             }
-            if (!r.idx->d_image) {
+            if (!sizing && !r.idx->d_image) {
                 delete b;
                 return fail(MPM_ESTATE, "mpm_batch_plan: request %u: index not uploaded", k);
             }
@@ -1173,7 +1202,11 @@ mpm_status mpm_batch_plan(const mpm_request *reqs, uint32_t count, mpm_batch **o
                 return st;
             }
             it.kind = batch_kind(r.idx, it.cfg);
-            const uint32_t key = launch_key(it.kind, it.cfg);
+            uint32_t key = launch_key(it.kind, it.cfg);
+            if (gram_batch_takes(r.idx, &r.variant, r.n)) {
+                it.kind = BK_GRAM;
+                key = GRAM_KEY;
+            }
             byw[key].push_back(it);
             if (r.variant.grid)
                 byw[key].back().cfg.grid = r.variant.grid;
@@ -1202,20 +1235,26 @@ mpm_status mpm_batch_plan(const mpm_request *reqs, uint32_t count, mpm_batch **o
             g.kind = items.front().kind;
             g.W = items.front().cfg.block_threads;
             std::map<const mpm_index *, uint32_t> slot;
+            std::vector<const mpm_index *> index;
             for (const Item &it : items) {
                 const mpm_request &r = reqs[it.req];
                 auto f = slot.find(it.ix);
                 uint32_t si;
                 if (f == slot.end()) {
-                    si = (uint32_t)g.idx.size();
+                    si = (uint32_t)index.size();
                     slot[it.ix] = si;
-                    BatchIndex bi;
-                    memset(&bi, 0, sizeof bi);
-                    if (it.ix->algo == MPM_ALGO_AC)
-                        bi.ac = ac_dev(it.ix);
-                    else
-                        bi.wm = wm_dev(it.ix);
-                    g.idx.push_back(bi);
+                    index.push_back(it.ix);
+                    if (g.kind == BK_GRAM) {
+                        g.gidx.push_back(gram_dev(it.ix));
+                    } else {
+                        BatchIndex bi;
+                        memset(&bi, 0, sizeof bi);
+                        if (it.ix->algo == MPM_ALGO_AC)
+                            bi.ac = ac_dev(it.ix);
+                        else
+                            bi.wm = wm_dev(it.ix);
+                        g.idx.push_back(bi);
+                    }
                 } else {
                     si = f->second;
                 }
@@ -1236,17 +1275,29 @@ mpm_status mpm_batch_plan(const mpm_request *reqs, uint32_t count, mpm_batch **o
                 g.ntiles += nt;
                 g.lds = std::max(g.lds, it.cfg.lds_bytes);
             }
+            if (g.kind == BK_GRAM) {
+                plan_gram_batch(index, &g.texts, &g.cut, g.grid_req, &g.grid, &g.lds);
+                g.ntiles = g.cut.parts.size();
+            }
             b->groups.push_back(std::move(g));
         }
         uint64_t off = 0;
         for (auto &g : b->groups) {
-            g.grid = batch_grid(g.kind, g.W, g.lds, g.ntiles, g.grid_req);
             g.text_off = off;
             off = align_up(off + g.texts.size() * sizeof(BatchText), 256);
             g.idx_off = off;
-            off = align_up(off + g.idx.size() * sizeof(BatchIndex), 256);
+            off = align_up(off + g.idx.size() * sizeof(BatchIndex) + g.gidx.size() * sizeof(GramDev), 256);
+            g.part_off = off;
+            off = align_up(off + g.cut.parts.size() * sizeof(GramPart), 256);
+            g.piece_off = off;
+            off = align_up(off + g.cut.pieces.size() * sizeof(uint2), 256);
+            g.ticket_off = off;
+            off = align_up(off + g.cut.tickets.size() * sizeof(uint32_t), 256);
             g.work_off = off;
             off = align_up(off + WS_HEADER_BYTES + 8 * g.ntiles, 256);
+            if (g.kind == BK_GRAM)
+                continue;
+            g.grid = batch_grid(g.kind, g.W, g.lds, g.ntiles, g.grid_req);
             g.stage_off = off;
             off = align_up(off + (uint64_t)g.grid * g.W * BATCH_STAGE_CAP * sizeof(mpm_match), 256);
         }
@@ -1271,6 +1322,15 @@ mpm_status mpm_batch_plan(const mpm_request *reqs, uint32_t count, mpm_batch **o
     }
 }
 
+extern "C" {
+
+mpm_status mpm_batch_plan(const mpm_request *reqs, uint32_t count, mpm_batch **out)
+{
+    if (!out || (!reqs && count))
+        return fail(MPM_EINVAL, "mpm_batch_plan: null argument");
+    return plan_batch(reqs, count, false, out);
+}
+
 uint64_t mpm_batch_device_bytes(const mpm_batch *b) { return b ? b->bytes : 0; }
 
 uint32_t mpm_batch_groups(const mpm_batch *b) { return b ? (uint32_t)b->groups.size() : 0; }
@@ -1291,7 +1351,7 @@ mpm_status mpm_batch_launch_key(const mpm_index *idx, const mpm_variant *variant
     if (cfg.supply)
         return fail(MPM_EUNSUPPORTED, "mpm_batch_launch_key: the supply-link walk runs in "
                     "single-text scans only");
-    *key = launch_key(batch_kind(idx, cfg), cfg);
+    *key = gram_batch_takes(idx, variant, 64) ? GRAM_KEY : launch_key(batch_kind(idx, cfg), cfg);
     g_err.clear();
     return MPM_OK;
 }
@@ -1305,11 +1365,19 @@ mpm_status mpm_batch_upload(mpm_batch *b, void *d_buf, uint64_t bytes, void *str
     if (bytes < b->bytes)
         return fail(MPM_ENOMEM, "mpm_batch_upload: buffer too small");
     std::vector<uint8_t> host(b->bytes, 0);
+    auto put = [&](uint64_t off, const auto &v) {
+        if (!v.empty())
+            memcpy(host.data() + off, v.data(), v.size() * sizeof v[0]);
+    };
     for (const auto &g : b->groups) {
-        memcpy(host.data() + g.text_off, g.texts.data(), g.texts.size() * sizeof(BatchText));
-        memcpy(host.data() + g.idx_off, g.idx.data(), g.idx.size() * sizeof(BatchIndex));
+        put(g.text_off, g.texts);
+        put(g.idx_off, g.idx);
+        put(g.idx_off, g.gidx);
+        put(g.part_off, g.cut.parts);
+        put(g.piece_off, g.cut.pieces);
+        put(g.ticket_off, g.cut.tickets);
     }
-    memcpy(host.data() + b->zero_off, b->zero_totals.data(), 8 * b->zero_totals.size());
+    put(b->zero_off, b->zero_totals);
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = hipMemcpyAsync(d_buf, host.data(), b->bytes, hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
@@ -1338,6 +1406,37 @@ static mpm_status ensure_side_streams(mpm_batch *b)
     return MPM_OK;
 }
 
+static mpm_status launch_group(const mpm_batch *b, const mpm_batch::Group &g, void *stream)
+{
+    if (g.kind == BK_GRAM) {
+        GramBatchDev gd;
+        memset(&gd, 0, sizeof gd);
+        gd.texts = (const BatchText *)(b->d_buf + g.text_off);
+        gd.idx = (const GramDev *)(b->d_buf + g.idx_off);
+        gd.parts = (const GramPart *)(b->d_buf + g.part_off);
+        gd.pieces = (const uint2 *)(b->d_buf + g.piece_off);
+        gd.tickets = (const uint32_t *)(b->d_buf + g.ticket_off);
+        gd.ntickets = g.cut.tickets.size();
+        gd.hdr = (uint32_t *)(b->d_buf + g.work_off);
+        gd.status = (uint64_t *)(b->d_buf + g.work_off + WS_HEADER_BYTES);
+        gd.lds_bytes = g.lds;
+        gd.us_per_tick = b->us_per_tick;
+        return launch_gram_batch(gd, g.grid, stream);
+    }
+    BatchDev bd;
+    memset(&bd, 0, sizeof bd);
+    bd.texts = (const BatchText *)(b->d_buf + g.text_off);
+    bd.idx = (const BatchIndex *)(b->d_buf + g.idx_off);
+    bd.ntexts = (uint32_t)g.texts.size();
+    bd.ntiles = g.ntiles;
+    bd.hdr = (uint32_t *)(b->d_buf + g.work_off);
+    bd.status = (uint64_t *)(b->d_buf + g.work_off + WS_HEADER_BYTES);
+    bd.stage = (mpm_match *)(b->d_buf + g.stage_off);
+    bd.stage_cap = BATCH_STAGE_CAP;
+    bd.us_per_tick = b->us_per_tick;
+    return launch_batch(bd, g.kind, g.W, g.grid, g.lds, stream);
+}
+
 mpm_status mpm_batch_run(const mpm_batch *cb, void *stream)
 {
     mpm_batch *b = const_cast<mpm_batch *>(cb);
@@ -1364,18 +1463,7 @@ mpm_status mpm_batch_run(const mpm_batch *cb, void *stream)
                 return fail(MPM_EHIP, "mpm_batch_run: stream wait failed");
             ls = b->side[gi];
         }
-        BatchDev bd;
-        memset(&bd, 0, sizeof bd);
-        bd.texts = (const BatchText *)(b->d_buf + g.text_off);
-        bd.idx = (const BatchIndex *)(b->d_buf + g.idx_off);
-        bd.ntexts = (uint32_t)g.texts.size();
-        bd.ntiles = g.ntiles;
-        bd.hdr = (uint32_t *)(b->d_buf + g.work_off);
-        bd.status = (uint64_t *)(b->d_buf + g.work_off + WS_HEADER_BYTES);
-        bd.stage = (mpm_match *)(b->d_buf + g.stage_off);
-        bd.stage_cap = BATCH_STAGE_CAP;
-        bd.us_per_tick = b->us_per_tick;
-        mpm_status st = launch_batch(bd, g.kind, g.W, g.grid, g.lds, ls);
+        mpm_status st = launch_group(b, g, ls);
         if (st)
             return st;
         if (fan && (hipEventRecord(b->done[gi], (hipStream_t)ls) != hipSuccess ||
@@ -1466,6 +1554,26 @@ static mpm_status tune_layout(const mpm_index *idx, uint64_t n, uint32_t copies,
     return MPM_OK;
 }
 
+// The plan of `copies` equal requests, as the filter runs them (sizing: no
+// buffers yet).
+static mpm_status tune_plan(const mpm_index *idx, const uint8_t *d_text, uint64_t n, uint32_t copies,
+                            const mpm_variant *v, mpm_match *d_out, uint64_t capacity, uint64_t *d_total,
+                            bool sizing, mpm_batch **out)
+{
+    mpm_request r;
+    memset(&r, 0, sizeof r);
+    r.idx = idx;
+    r.d_text = d_text;
+    r.n = n;
+    if (v)
+        r.variant = *v;
+    r.d_out = d_out;
+    r.capacity = capacity;
+    r.d_total = d_total;
+    const std::vector<mpm_request> reqs(copies, r);
+    return plan_batch(reqs.data(), copies, sizing, out);
+}
+
 uint64_t mpm_tune_work_bytes(const mpm_index *idx, uint64_t n, uint32_t copies,
                              const mpm_variant *v)
 {
@@ -1474,6 +1582,17 @@ uint64_t mpm_tune_work_bytes(const mpm_index *idx, uint64_t n, uint32_t copies,
     uint32_t grid;
     if (tune_layout(idx, n, copies, v, &cfg, &nt, &io, &wo, &so, &grid, &bytes))
         return 0;
+    if (nt && gram_batch_takes(idx, v, n)) {
+        try {
+            mpm_batch *b = nullptr;
+            if (tune_plan(idx, nullptr, n, copies, v, nullptr, 0, nullptr, true, &b))
+                return 0;
+            bytes = b->bytes;
+            mpm_batch_free(b);
+        } catch (const std::bad_alloc &) {
+            return 0;
+        }
+    }
     return bytes;
 }
 
@@ -1496,6 +1615,18 @@ mpm_status mpm_tune_time(const mpm_index *idx, const uint8_t *d_text, uint64_t n
     mpm_status st = tune_layout(idx, n, copies, v, &cfg, &nt, &io, &wo, &so, &grid, &bytes);
     if (st)
         return st;
+    mpm_batch *plan = nullptr;
+    if (nt && gram_batch_takes(idx, v, n)) {
+        try {
+            st = tune_plan(idx, d_text, n, copies, v, d_out, capacity, d_total, false, &plan);
+        } catch (const std::bad_alloc &) {
+            st = fail(MPM_ENOMEM, "mpm_tune_time: out of host memory");
+        }
+        if (st)
+            return st;
+        bytes = plan->bytes;
+    }
+    std::unique_ptr<mpm_batch, void (*)(mpm_batch *)> hold(plan, mpm_batch_free);
     if (work_bytes < bytes)
         return fail(MPM_ENOMEM, "mpm_tune_time: workspace of %llu bytes, need %llu",
                     (unsigned long long)work_bytes, (unsigned long long)bytes);
@@ -1505,6 +1636,13 @@ mpm_status mpm_tune_time(const mpm_index *idx, const uint8_t *d_text, uint64_t n
     if (nt == 0) {
         *ms_out = 0.f;
         return MPM_OK;
+    }
+    hipStream_t s = (hipStream_t)stream;
+    if (plan) {
+        st = mpm_batch_upload(plan, d_work, work_bytes, stream);
+        if (st)
+            return st;
+        return time_launches([&] { return launch_group(plan, plan->groups.front(), stream); }, s, reps, ms_out);
     }
     try {
         std::vector<uint8_t> host(wo + WS_HEADER_BYTES, 0);
@@ -1522,7 +1660,6 @@ mpm_status mpm_tune_time(const mpm_index *idx, const uint8_t *d_text, uint64_t n
             bi->ac = ac_dev(idx);
         else
             bi->wm = wm_dev(idx);
-        hipStream_t s = (hipStream_t)stream;
         hipError_t e = hipMemcpyAsync(d_work, host.data(), host.size(), hipMemcpyHostToDevice, s);
         if (e != hipSuccess)
             return fail(MPM_EHIP, "mpm_tune_time: upload: %s", hipGetErrorString(e));
@@ -1538,24 +1675,8 @@ mpm_status mpm_tune_time(const mpm_index *idx, const uint8_t *d_text, uint64_t n
         bd.stage = (mpm_match *)((uint8_t *)d_work + so);
         bd.stage_cap = BATCH_STAGE_CAP;
         const uint32_t kind = batch_kind(idx, cfg);
-        hipEvent_t a, z;
-        if (hipEventCreate(&a) != hipSuccess || hipEventCreate(&z) != hipSuccess)
-            return fail(MPM_EHIP, "mpm_tune_time: event creation failed");
-        // warm-up, then `reps` launches between two events: the mean launch
-        st = launch_batch(bd, kind, cfg.block_threads, grid, cfg.lds_bytes, stream);
-        (void)hipEventRecord(a, s);
-        for (uint32_t r = 0; r < reps && st == MPM_OK; r++)
-            st = launch_batch(bd, kind, cfg.block_threads, grid, cfg.lds_bytes, stream);
-        (void)hipEventRecord(z, s);
-        float ms = 0.f;
-        if (st == MPM_OK && hipEventSynchronize(z) == hipSuccess)
-            (void)hipEventElapsedTime(&ms, a, z);
-        (void)hipEventDestroy(a);
-        (void)hipEventDestroy(z);
-        if (st)
-            return st;
-        *ms_out = ms / (float)reps;
-        return MPM_OK;
+        return time_launches([&] { return launch_batch(bd, kind, cfg.block_threads, grid, cfg.lds_bytes, stream); }, s,
+                             reps, ms_out);
     } catch (const std::bad_alloc &) {
         return fail(MPM_ENOMEM, "mpm_tune_time: out of host memory");
     }

@@ -211,6 +211,7 @@ enum {
     BK_AC16_HOT = 5,
     BK_WM_HOT = 6,
     BK_AC32_HOT = 7,
+    BK_GRAM = 8,   // the q-gram filter (its own kernel and descriptors)
     BK_WALK_MASK = 0x7f,
     BK_SWAR = 0x80
 };
@@ -240,6 +241,25 @@ struct BatchDev {
     mpm_match *stage;     // staging area (null when stage_cap is 0)
     uint32_t stage_cap;   // staged occurrences per lane
     float us_per_tick;    // microseconds per wall-clock tick (timed requests)
+};
+
+// Filter launches: blocks [b0, b0 + nb) of a text.
+struct GramPart {
+    uint32_t text;        // into the launch's BatchText array
+    uint32_t b0, nb;
+};
+
+struct GramBatchDev {
+    const BatchText *texts;    // index: into idx; tile_begin, ntiles: the text's parts
+    const GramDev *idx;
+    const GramPart *parts;
+    const uint2 *pieces;       // a wave's parts [x, y); 16 pieces per ticket
+    const uint32_t *tickets;   // a ticket's index
+    uint64_t ntickets;
+    uint32_t *hdr;
+    uint64_t *status;          // one word per part
+    uint32_t lds_bytes;        // per workgroup
+    float us_per_tick;
 };
 
 // Staged occurrences per lane: single-text scans stage a lane's whole range
@@ -390,6 +410,16 @@ void id_csr(const mpm_index *ix, const uint32_t **uoff, const uint32_t **uids);
 bool gram_takes(const mpm_index *ix, const mpm_variant *v, uint64_t n);
 bool gram_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, uint32_t lo, GramCfg *g);
 mpm_status gram_launch(const mpm_index *ix, const GramCfg &g, const ScanDev &sd, void *stream);
+GramDev gram_dev(const mpm_index *ix);
+struct GramPieces {
+    std::vector<GramPart> parts;
+    std::vector<uint2> pieces;
+    std::vector<uint32_t> tickets;
+};
+bool gram_batch_takes(const mpm_index *ix, const mpm_variant *v, uint64_t n);
+void plan_gram_batch(const std::vector<const mpm_index *> &index, std::vector<BatchText> *texts,
+                     GramPieces *out, uint32_t grid_req, uint32_t *grid, uint32_t *lds_bytes);
+mpm_status launch_gram_batch(const GramBatchDev &bd, uint32_t grid, void *stream);
 bool direct_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, uint32_t lo, GramCfg *g);
 mpm_status direct_launch(const mpm_index *ix, const GramCfg &g, const ScanDev &sd, void *stream);
 uint32_t batch_kind(const mpm_index *ix, const LaunchCfg &c);

@@ -33,6 +33,10 @@
 // AC 135 -> 69; 32 MiB, lengths 8-32, WM 2132 -> 30.
 #include "mpm_gram.h"
 
+#include <cmath>
+#include <functional>
+#include <queue>
+
 namespace mpm {
 
 namespace {
@@ -48,6 +52,13 @@ constexpr uint32_t GBLOCK = 1024 * GN;              // text bytes per wave and s
 static_assert(256 / 64 * GBLOCK >= GRAM_CHUNK_MIN, "workspace bound");
 constexpr uint32_t WV_ITEMS = (64 * GN + 8) * 4;
 constexpr uint32_t WV_HITS = WV_ITEMS + 64 * 8;
+
+// LDS bytes of one wave's buffers in a batched launch of lds_bytes per
+// workgroup, beside an index's bits.
+__host__ __device__ constexpr uint32_t batch_wave_bytes(uint32_t lds_bytes, uint32_t bit_bytes)
+{
+    return (lds_bytes - GBITS_OFF - bit_bytes) / 16 & ~15u;
+}
 
 // Write the pairs of up to 64 occurrences (one per active lane, in lane
 // order) from output slot o on; o moves past them.
@@ -80,6 +91,23 @@ struct GramScan {
     uint32_t wv;    // LDS offset of this wave's buffers
     uint32_t hcap;
     uint32_t amask, bsh, wmask;
+
+    __device__ __forceinline__ void bind(const GramDev &dev, const uint8_t *t, uint64_t n)
+    {
+        a = dev;
+        text.lo = (uint32_t)((uintptr_t)t & 15u);
+        text.p = (glb_cptr<uint8_t>)(t - text.lo);
+        text.hi = n + text.lo;
+        im.uoff = (glb_cptr<uint32_t>)a.uoff;
+        im.uids = (glb_cptr<uint32_t>)a.uids;
+        im.lds_uoff = 0;
+        im.lds_uids = 0;
+        im.dupfree = 0;
+        im.n_single = a.n_single;
+        wmask = (1u << (2 * a.q - 5)) - 1u;
+        amask = wmask << 2;
+        bsh = 2 * a.q - 3;
+    }
 
     // Whether the len >= 4 bytes at view position s are string (row, len):
     // whole 16-, 8- or 4-byte pieces, the last one ending with the string.
@@ -292,6 +320,39 @@ struct GramScan {
         } while (iw < tot);
     }
 
+    // Blocks [b0, b1): count, get the output slot of this wave's first pair
+    // from place(number of ids), write the pairs.
+    template <class F>
+    __device__ __forceinline__ void part(uint64_t b0, uint64_t b1, mpm_match *out, uint64_t cap, F place) const
+    {
+        const uint32_t lane = threadIdx.x & 63u;
+        uint32_t nh, nid;
+        uint64_t o = 0;
+#pragma unroll 1
+        for (uint32_t pass = 0; pass < 2; ++pass) {
+            run(pass != 0, hidden(b0), b1, nh, nid, out, cap, o);
+            if (pass)
+                break;
+#pragma unroll
+            for (int k = 32; k >= 1; k >>= 1)
+                nid += __shfl_xor(nid, k, 64);
+            o = place(nid);
+            if (nh == 0 || o >= cap)
+                break;
+            if (nh <= hcap) {
+                wave_sync();
+                for (uint32_t r = 0; r < nh && o < cap; r += 64) {
+                    const bool act = r + lane < nh;
+                    v2u h = {0, 0};
+                    if (act)
+                        h = lds_at<v2u>(wv + WV_HITS)[r + lane];
+                    write_hits(out, cap, o, act, h.x, h.y, im);
+                }
+                break;
+            }
+        }
+    }
+
     // Bytewise check of one (start, string) per active lane, in text order.
     __device__ __forceinline__ void check(bool direct, bool act, uint64_t sv, uint32_t u, uint32_t &nh, uint32_t &nid,
                                           uint32_t &last, mpm_match *out, uint64_t cap, uint64_t &o) const
@@ -320,7 +381,6 @@ __global__ __launch_bounds__(W) void gram_kernel(GramDev a, ScanDev sd, uint32_t
     uint32_t *const hdr = sd.hdr;
     constexpr uint32_t NW = W / 64;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t lane = threadIdx.x & 63u;
 
     if (threadIdx.x == 0) {
         s_tile = take_ticket(hdr);
@@ -330,22 +390,9 @@ __global__ __launch_bounds__(W) void gram_kernel(GramDev a, ScanDev sd, uint32_t
     load_groups(a.grp);
 
     GramScan<TL, Var> sc;
-    sc.a = a;
-    const uint64_t addr = (uint64_t)(uintptr_t)sd.single.text;
-    sc.text.lo = (uint32_t)(addr & 15u);
-    sc.text.p = (glb_cptr<uint8_t>)(sd.single.text - sc.text.lo);
-    sc.text.hi = sd.single.n + sc.text.lo;
-    sc.im.uoff = (glb_cptr<uint32_t>)a.uoff;
-    sc.im.uids = (glb_cptr<uint32_t>)a.uids;
-    sc.im.lds_uoff = 0;
-    sc.im.lds_uids = 0;
-    sc.im.dupfree = 0;
-    sc.im.n_single = a.n_single;
+    sc.bind(a, sd.single.text, sd.single.n);
     sc.wv = GBITS_OFF + a.bit_bytes + wave * wave_bytes;
     sc.hcap = hits;
-    sc.wmask = (1u << (2 * a.q - 5)) - 1u;
-    sc.amask = sc.wmask << 2;
-    sc.bsh = 2 * a.q - 3;
     const uint64_t ntiles = sd.ntiles;
     const uint64_t cap = sd.single.cap;
 
@@ -356,32 +403,10 @@ __global__ __launch_bounds__(W) void gram_kernel(GramDev a, ScanDev sd, uint32_t
             break;
         const uint64_t b0 = min((g * NW + wave) * blocks, nblocks);
         const uint64_t b1 = min(b0 + blocks, nblocks);
-        uint32_t nh, nid;
-        uint64_t o = 0;
-#pragma unroll 1
-        for (uint32_t pass = 0; pass < 2; ++pass) {
-            sc.run(pass != 0, hidden(b0), b1, nh, nid, sd.single.out, cap, o);
-            if (pass)
-                break;
-#pragma unroll
-            for (int k = 32; k >= 1; k >>= 1)
-                nid += __shfl_xor(nid, k, 64);
-            o = wave_offset<W>(nid, s_scan, sd.status, g, ntiles, sd.single.total, s_epoch | GRAM_EPOCH,
-                               &hdr[WS_ERR]);
-            if (nh == 0 || o >= cap)
-                break;
-            if (nh <= hits) {
-                wave_sync();
-                for (uint32_t r = 0; r < nh && o < cap; r += 64) {
-                    const bool act = r + lane < nh;
-                    v2u h = {0, 0};
-                    if (act)
-                        h = lds_at<v2u>(sc.wv + WV_HITS)[r + lane];
-                    write_hits(sd.single.out, cap, o, act, h.x, h.y, sc.im);
-                }
-                break;
-            }
-        }
+        sc.part(b0, b1, sd.single.out, cap, [&](uint32_t nid) {
+            return wave_offset<W>(nid, s_scan, sd.status, g, ntiles, sd.single.total, s_epoch | GRAM_EPOCH,
+                                  &hdr[WS_ERR]);
+        });
         if (gridDim.x >= ntiles)  // one chunk per workgroup
             break;
         if (threadIdx.x == 0)
@@ -393,6 +418,113 @@ __global__ __launch_bounds__(W) void gram_kernel(GramDev a, ScanDev sd, uint32_t
         return;
     }
     finish_launch(hdr, s_epoch);
+}
+
+// A descriptor at a uniform address that no launch writes, by scalar loads.
+template <class T>
+__device__ __forceinline__ T uniform_load(const T *p)
+{
+    typedef const __attribute__((address_space(4))) uint32_t *words;
+    uint32_t w[sizeof(T) / 4];
+#pragma unroll
+    for (uint32_t k = 0; k < sizeof(T) / 4; ++k)
+        w[k] = ((words)(uintptr_t)p)[k];
+    T t;
+    __builtin_memcpy(&t, w, sizeof t);
+    return t;
+}
+
+// Batched texts. A wave takes a piece: parts (runs of blocks) of one or more
+// texts of an index, of about equal expected time in every piece
+// (plan_gram_batch). Sixteen pieces of an index are a ticket; the workgroup
+// copies the index's bits to LDS, and its waves don't wait for each other
+// until the next ticket: each looks back over the parts of its own texts.
+// A piece's last part, which the next piece may go on from, is run first, so
+// that a piece that starts inside a text finds the counts before it early.
+// (One workgroup chunk per text, as the walkers have it, leaves the chip idle
+// for short texts; a unit per wave and text left 222 of 4096 waves with less
+// than a quarter of their time's work and the others with twice it, 198 us.)
+//
+// Measured on 256 EST-shaped texts of 1 KiB to 4 MiB (120 MB) and eight sets
+// of 115 to 4648 strings of 8 to 32 characters, replayed graph: @@@.
+template <int TL>
+__device__ __forceinline__ void batch_part(const GramDev &dev, const TextDesc &td, uint64_t g, const GramPart &part,
+                                           uint32_t wv, uint32_t hits, uint32_t epoch, uint32_t *hdr, uint64_t *status)
+{
+    GramScan<TL, false> sc;
+    sc.bind(dev, td.text, td.n);
+    sc.wv = wv;
+    sc.hcap = hits;
+    const uint64_t first = td.tile_begin, last = first + td.ntiles - 1;
+    uint64_t *const total = td.total;
+    const uint64_t b0 = part.b0, b1 = b0 + part.nb;
+    sc.part(b0, b1, td.out, td.cap, [&](uint32_t nid) {
+        const uint64_t agg = __builtin_amdgcn_readfirstlane(nid);
+        const uint64_t o = uniform64(look_back(status, g, first, agg, epoch, &hdr[WS_ERR]));
+        if (g == last && (threadIdx.x & 63u) == 0)
+            *total = o + agg;
+        return o;
+    });
+}
+
+__global__ __launch_bounds__(1024) void gram_batch_kernel(GramBatchDev bd)
+{
+    extern __shared__ __align__(16) uint8_t smem[];
+    if (!lds_layout_ok(smem, bd.hdr))
+        return;
+    LdsHdr *const H = (LdsHdr *)lds_at<LdsHdr>(LDS_HDR_OFF);
+    uint64_t &s_tile = H->tile;
+    uint32_t &s_epoch = H->epoch;
+    constexpr uint32_t NW = 1024 / 64;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (threadIdx.x == 0)
+        s_epoch = __hip_atomic_load(&bd.hdr[WS_EPOCH], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint32_t loaded = 0xffffffffu;
+    while (true) {
+        if (threadIdx.x == 0)
+            s_tile = take_ticket(bd.hdr);
+        __syncthreads();
+        const uint64_t t = uniform64(s_tile);
+        if (t >= bd.ntickets)
+            break;
+        const uint32_t epoch = __builtin_amdgcn_readfirstlane(s_epoch);
+        const uint2 range = uniform_load((const uint2 *)bd.pieces + t * NW + wave);
+        const uint32_t ix = uniform_load(bd.tickets + t);
+        const GramDev dev = uniform_load(bd.idx + ix);
+        if (ix != loaded) {
+            copy_to_lds<1024>(GBITS_OFF, (const uint8_t *)dev.bits, dev.bit_bytes);
+            load_groups(bd.idx[ix].grp);
+            loaded = ix;
+        }
+        __syncthreads();
+        const uint32_t wave_bytes = batch_wave_bytes(bd.lds_bytes, dev.bit_bytes);
+        const uint32_t wv = GBITS_OFF + dev.bit_bytes + wave * wave_bytes;
+        const uint32_t hits = (wave_bytes - WV_HITS) / 8;
+#pragma unroll 1
+        for (uint32_t k = range.y; k-- > range.x;) {
+            const GramPart p = uniform_load(bd.parts + k);
+            const BatchText bt = uniform_load(bd.texts + p.text);
+            uint64_t t0 = 0;
+            if (bt.cost)
+                t0 = wall_clock64();
+            switch (dev.t_log) {
+            case 0: batch_part<0>(dev, bt.td, k, p, wv, hits, epoch, bd.hdr, bd.status); break;
+            case 1: batch_part<1>(dev, bt.td, k, p, wv, hits, epoch, bd.hdr, bd.status); break;
+            case 2: batch_part<2>(dev, bt.td, k, p, wv, hits, epoch, bd.hdr, bd.status); break;
+            case 3: batch_part<3>(dev, bt.td, k, p, wv, hits, epoch, bd.hdr, bd.status); break;
+            default: batch_part<4>(dev, bt.td, k, p, wv, hits, epoch, bd.hdr, bd.status); break;
+            }
+            // a timed request: a wave's time on a part counts as a sixteenth
+            // of a workgroup's
+            if (bt.cost && (threadIdx.x & 63u) == 0) {
+                const float us = (float)(wall_clock64() - t0) * bd.us_per_tick;
+                atomicAdd(&bt.cost[0], us / (float)(gridDim.x * NW));
+                atomicMax((uint32_t *)&bt.cost[1], __float_as_uint(us));  // order of >= 0 floats
+            }
+        }
+        __syncthreads();
+    }
+    finish_launch(bd.hdr, s_epoch);
 }
 
 template <int W>
@@ -478,10 +610,8 @@ bool gram_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, uint32_t
     return (uint64_t)(blocks * GBLOCK + 16) * std::max<uint64_t>(1, ix->max_dup) < (1ull << 32);
 }
 
-mpm_status gram_launch(const mpm_index *ix, const GramCfg &g, const ScanDev &sd, void *stream)
+GramDev gram_dev(const mpm_index *ix)
 {
-    if (g.direct)
-        return direct_launch(ix, g, sd, stream);
     const mpm_index::Gram &G = ix->gram;
     GramDev a;
     const uint8_t *img = ix->d_image;
@@ -498,15 +628,161 @@ mpm_status gram_launch(const mpm_index *ix, const GramCfg &g, const ScanDev &sd,
     a.m = ix->m;
     a.n_single = ix->n_single;
     a.grp = id_groups(ix);
+    return a;
+}
+
+mpm_status gram_launch(const mpm_index *ix, const GramCfg &g, const ScanDev &sd, void *stream)
+{
+    if (g.direct)
+        return direct_launch(ix, g, sd, stream);
+    GramDev a = gram_dev(ix);
     ScanDev s = sd;
     s.ntiles = g.nchunks;
     uint32_t blocks = g.blocks, hits = g.hits, wave_bytes = g.wave_bytes;
     uint64_t nblocks = g.nblocks;
     void *args[] = {&a, &s, &blocks, &nblocks, &hits, &wave_bytes};
-    const hipError_t e = hipLaunchKernel(kernel_of(g.W, G.t_log, ix->var != 0), dim3(g.grid), dim3(g.W),
+    const hipError_t e = hipLaunchKernel(kernel_of(g.W, ix->gram.t_log, ix->var != 0), dim3(g.grid), dim3(g.W),
                                          args, g.lds_bytes, (hipStream_t)stream);
     if (e != hipSuccess)
         return fail(MPM_EHIP, "scan launch: %s", hipGetErrorString(e));
+    return MPM_OK;
+}
+
+// Whether a batched request runs through the filter. (Sets without one whose
+// single scans use direct addressing stay with the walkers.)
+bool gram_batch_takes(const mpm_index *ix, const mpm_variant *v, uint64_t n)
+{
+    return ix->gram.ok && !ix->var && n < (1ull << 32) && gram_takes(ix, v, n) &&
+           GBITS_OFF + ix->gram.bit_bytes + 16 * (WV_HITS + 16 * 8) <= (uint32_t)limits().max_lds &&
+           (uint64_t)(GBLOCK + 16) * std::max<uint64_t>(1, ix->max_dup) < (1ull << 32);
+}
+
+// Blocks of a batched text (whatever its alignment).
+static uint64_t batch_blocks(uint64_t n) { return (n + 15 + GBLOCK - 1) / GBLOCK; }
+
+// Cut the texts (those of an index together) into pieces for one wave each.
+// A block takes a wave about 1.5 us for the sparsest sets, 0.85 us per unit of
+// the filter's cost and 300 us per occurrence and byte (timed requests of 9 to
+// 23 MB, costs 1.6 to 17: 1.6 to 39 us per block), a part's first load and
+// offset about 2 us more. Of the piece lengths around the average load of a
+// wave the one is taken whose tickets, longest first, end earliest; one round
+// in most cases, but the occurrence lists bound the blocks of a part, and
+// with them a dense set's pieces.
+void plan_gram_batch(const std::vector<const mpm_index *> &index, std::vector<BatchText> *texts,
+                     GramPieces *out, uint32_t grid_req, uint32_t *grid, uint32_t *lds_bytes)
+{
+    const DeviceLimits lim = limits();
+    const uint32_t lds = (uint32_t)lim.max_lds & ~15u;
+    const uint64_t slots = grid_req ? grid_req : std::max(1, lim.cus);  // workgroups of 1024 threads: one per CU
+    const double part_us = 2.0, ticket_us = 4.0;
+    std::vector<double> w;       // us per block
+    std::vector<uint64_t> most;  // blocks of a part
+    std::vector<std::vector<uint32_t>> of(index.size());
+    for (const mpm_index *ix : index) {
+        const mpm_index::Gram &G = ix->gram;
+        w.push_back(std::max(1.5, 0.85 * G.cost + 300.0 * G.hit));
+        const double fit = 0.6 * ((batch_wave_bytes(lds, G.bit_bytes) - WV_HITS) / 8) / (GBLOCK * G.hit);
+        const uint64_t ids = ((1ull << 32) - 1) / std::max<uint64_t>(1, ix->max_dup);  // a part's count of ids: 32 bits
+        most.push_back(std::max<uint64_t>(1, std::min<uint64_t>(fit > 4096 ? 4096 : (uint64_t)fit, (ids - 16) / GBLOCK)));
+    }
+    double sum = 0;
+    for (size_t i = 0; i < texts->size(); i++) {
+        const BatchText &bt = (*texts)[i];
+        of[bt.index].push_back((uint32_t)i);
+        sum += w[bt.index] * (double)batch_blocks(bt.td.n) + part_us;
+    }
+    // The pieces of index k, each at most len long where its parts allow:
+    // piece() starts one, part(text, b0, nb) adds to it. No piece has two
+    // parts of one text (the later one would wait for the earlier).
+    auto cut = [&](uint32_t k, double len, auto piece, auto part) {
+        double room = 0;
+        for (uint32_t i : of[k]) {
+            const uint64_t nb = batch_blocks((*texts)[i].td.n);
+            for (uint64_t b = 0; b < nb;) {
+                if (b || room < part_us + w[k]) {
+                    piece();
+                    room = len;
+                }
+                const uint64_t c = room < part_us + w[k] ? 1 : (uint64_t)((room - part_us) / w[k]);
+                const uint64_t take = std::min({c, most[k], nb - b});
+                part(i, b, take);
+                room -= part_us + w[k] * (double)take;
+                b += take;
+            }
+        }
+    };
+    // End of the last ticket; order: indexes, those of the longest tickets first.
+    std::vector<uint32_t> order(index.size());
+    auto plan = [&](double len) {
+        std::vector<uint64_t> pieces(index.size(), 0);
+        std::vector<double> longest(index.size(), 0.0);
+        for (uint32_t k = 0; k < index.size(); k++) {
+            double cur = 0;
+            cut(k, len, [&] { pieces[k]++; cur = 0; },
+                [&](uint32_t, uint64_t, uint64_t take) {
+                    cur += part_us + w[k] * (double)take;
+                    longest[k] = std::max(longest[k], cur);
+                });
+            order[k] = k;
+        }
+        std::stable_sort(order.begin(), order.end(), [&](uint32_t x, uint32_t y) { return longest[x] > longest[y]; });
+        std::priority_queue<double, std::vector<double>, std::greater<double>> busy;
+        double end = 0;
+        for (uint32_t k : order)
+            for (uint64_t t = 0; t < (pieces[k] + 15) / 16; t++) {
+                double at = 0;
+                if (busy.size() >= slots) {
+                    at = busy.top();
+                    busy.pop();
+                }
+                busy.push(at + ticket_us + longest[k]);
+                end = std::max(end, at + ticket_us + longest[k]);
+            }
+        return end;
+    };
+    const double mean = sum / (16.0 * (double)slots);
+    double best = 1e300, len = mean;
+    for (int k = -8; k <= 12; k++) {
+        const double l = mean * exp2(k / 8.0), end = plan(l);
+        if (end < best) {
+            best = end;
+            len = l;
+        }
+    }
+    (void)plan(len);
+    for (uint32_t k : order) {
+        std::vector<uint32_t> first;
+        cut(k, len, [&] { first.push_back((uint32_t)out->parts.size()); },
+            [&](uint32_t i, uint64_t b0, uint64_t take) {
+                TextDesc &td = (*texts)[i].td;
+                if (b0 == 0) {
+                    td.tile_begin = out->parts.size();
+                    td.ntiles = 0;
+                }
+                td.ntiles++;
+                out->parts.push_back(GramPart{i, (uint32_t)b0, (uint32_t)take});
+            });
+        const uint32_t end = (uint32_t)out->parts.size();
+        for (size_t j = 0; j < (first.size() + 15) / 16 * 16; j++) {
+            const uint32_t lo = j < first.size() ? first[j] : end, hi = j + 1 < first.size() ? first[j + 1] : end;
+            out->pieces.push_back(make_uint2(lo, hi));
+        }
+        out->tickets.resize(out->pieces.size() / 16, k);
+    }
+    *grid = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(slots, out->tickets.size()));
+    *lds_bytes = lds;
+}
+
+mpm_status launch_gram_batch(const GramBatchDev &bd, uint32_t grid, void *stream)
+{
+    const void *k = (const void *)gram_batch_kernel;
+    if (bd.lds_bytes > 65536)
+        (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bd.lds_bytes);
+    GramBatchDev b = bd;
+    void *args[] = {&b};
+    const hipError_t e = hipLaunchKernel(k, dim3(grid), dim3(1024), args, bd.lds_bytes, (hipStream_t)stream);
+    if (e != hipSuccess)
+        return fail(MPM_EHIP, "batch launch: %s", hipGetErrorString(e));
     return MPM_OK;
 }
 
