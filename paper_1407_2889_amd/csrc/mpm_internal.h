@@ -116,11 +116,13 @@ struct WmDev {
 struct GramEnt {      // one (string, offset) of a gram
     uint32_t key;     // codes of the string's first characters (at most 16)
     uint32_t mask;    // the bits of key that count
-    uint32_t meta;    // string << 4 | offset
+    uint32_t meta;    // string << 5 | plain << 4 | offset; plain: the string has at most 16
+                      // characters, all strings have its length, and each of them is
+                      // the main byte of its code, so that key tells the bytes
     uint32_t next;    // next entry of the same gram (all ones: none)
 };
 struct GramDev {
-    const uint32_t *bits;     // 4^q bits, copied to LDS
+    const uint32_t *bits;     // 4^q bits (and the second half of words), copied to LDS
     const uint2 *words;       // per word of bits: (the word, grams before it)
     const GramEnt *ents;      // the first entry of gram number k at k, the others after them;
                               // a chain's offsets descend, longer strings first
@@ -129,7 +131,9 @@ struct GramDev {
     const uint32_t *uoff;
     const uint32_t *uids;
     uint32_t q, t_log, code_shift;
-    uint32_t bit_bytes;       // bytes of bits (multiple of 16)
+    uint32_t bit_bytes;       // bytes copied to LDS (multiple of 16)
+    uint32_t rank_off;        // where the second half of words starts there (0: not copied)
+    uint32_t main4;           // main byte of code k in byte k
     uint32_t m;               // shortest string
     uint32_t n_single;
     IdGroups grp;
@@ -325,7 +329,7 @@ struct mpm_index {
 
     // q-gram filter (mpm_gram.cpp); ok = 0: the set has none
     struct Gram {
-        uint32_t ok = 0, q = 0, t_log = 0, code_shift = 0, bit_bytes = 0;
+        uint32_t ok = 0, q = 0, t_log = 0, code_shift = 0, bit_bytes = 0, ranked = 0, main4 = 0;
         double cost = 0; // expected vector instructions per text byte (mpm_gram.cpp)
         double hit = 0;  // expected occurrences per text byte
         uint64_t off_bits = 0, off_words = 0, off_ents = 0, off_strs = 0, off_rows = 0;
@@ -410,7 +414,7 @@ void id_csr(const mpm_index *ix, const uint32_t **uoff, const uint32_t **uids);
 bool gram_takes(const mpm_index *ix, const mpm_variant *v, uint64_t n);
 bool gram_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, uint32_t lo, GramCfg *g);
 mpm_status gram_launch(const mpm_index *ix, const GramCfg &g, const ScanDev &sd, void *stream);
-GramDev gram_dev(const mpm_index *ix);
+GramDev gram_dev(const mpm_index *ix, uint32_t W = 1024);
 struct GramPieces {
     std::vector<GramPart> parts;
     std::vector<uint2> pieces;

@@ -13,11 +13,12 @@
 //   2. One LDS bit per sample (every t-th position) tells whether the q-gram
 //      there occurs in a string at an offset below t: a shift, a mask, a
 //      ds_read, two shifts, one v_alignbit to collect the bit.
-//   3. The block's candidates, in text order, are dealt to the lanes 64 at a
+//   3. The block's candidates, in text order, are dealt to the lanes 128 at a
 //      time; each walks its gram's chain of (string, offset) entries and
 //      compares the codes of the string's first 16 characters.
-//   4. What remains is compared byte by byte, 16 bytes per step; occurrences
-//      go to a list in LDS in text order (ballots keep the order).
+//   4. What remains is compared byte by byte, with bytes made from the codes
+//      where those tell them, else with the string's row; occurrences go to a
+//      list in LDS in text order (ballots keep the order).
 //   5. Per chunk: wave counts -> workgroup offsets -> decoupled look-back, as
 //      the walkers do, then the wave writes its pairs 64 at a time. A wave
 //      whose list overflows runs its part again and writes as it goes.
@@ -27,10 +28,10 @@
 // (t = 8, q = 9, one candidate per 260 bytes) that is below what HBM asks for.
 //
 // Measured (EST-shaped text, walkers before, filter after, us): 256 MiB,
-// d = 1000, m = 16: AC 102 -> 67, WM 100 -> 67 (4.0 TB/s of text); 128 MiB,
-// d = 10k, m = 16, AC 366 -> 48; 64 MiB, d = 100k, m = 16, WM 3577 -> 109;
-// 64 MiB, d = 1000, m = 8 with counts, WM 422 -> 99; 128 MiB, lengths 8-32,
-// AC 135 -> 69; 32 MiB, lengths 8-32, WM 2132 -> 30.
+// d = 1000, m = 16: AC 102 -> 63, WM 99 -> 63 (4.2 TB/s of text); 128 MiB,
+// d = 10k, m = 16, AC 366 -> 48; 64 MiB, d = 100k, m = 16, WM 3577 -> 97;
+// 64 MiB, d = 1000, m = 8 with counts, WM 422 -> 91; 128 MiB, lengths 8-32,
+// AC 135 -> 67; 32 MiB, lengths 8-32, WM 2132 -> 31.
 #include "mpm_gram.h"
 
 #include <cmath>
@@ -240,84 +241,138 @@ struct GramScan {
             uint32_t tot;
             const uint32_t pre = wave_excl_sum(cnt, tot);
 #pragma unroll 1
-            for (uint32_t win = 0; win < tot; win += 64) {
+            for (uint32_t win = 0; win < tot; win += 128) {
                 wave_sync();
-                uint32_t rk = pre - win;  // below 64: this window's slot
+                uint32_t rk = pre - win;  // below 128: this window's slot
 #pragma unroll
                 for (uint32_t h = 0; h < NM; ++h)
                     for (uint32_t mm = mk[h]; mm; mm &= mm - 1, ++rk)
-                        if (rk < 64)
+                        if (rk < 128)
                             slot[rk] = lane * NS + 32 * h + (uint32_t)__builtin_ctz(mm);
                 wave_sync();
-                const bool active = lane < tot - win;
-                uint32_t p = 0, code = 0, pv = 0;
-                if (active) {
-                    p = slot[lane] << TL;  // sample, relative to the block
-                    const uint32_t wi = p >> 4, sub = 2 * (p & 15);
-                    const uint32_t A = cw[3 + wi], B = cw[4 + wi], C = cw[5 + wi];
-                    code = __builtin_amdgcn_alignbit(C, B, sub);
-                    pv = __builtin_amdgcn_alignbit(B, A, sub);
-                }
-                candidates(direct, b * GBLOCK, active, p, code, pv, nh, nid, last, out, cap, o);
+                if (tot - win > 64)
+                    candidates<2>(direct, b * GBLOCK, tot - win, nh, nid, last, out, cap, o);
+                else
+                    candidates<1>(direct, b * GBLOCK, tot - win, nh, nid, last, out, cap, o);
             }
         }
     }
 
-    // One batch of candidates, one per active lane in text order.
-    __device__ __forceinline__ void candidates(bool direct, uint64_t base, bool active, uint32_t p, uint32_t code,
-                                               uint32_t pv, uint32_t &nh, uint32_t &nid, uint32_t &last,
-                                               mpm_match *out, uint64_t cap, uint64_t &o) const
+    // The first min(n, 64 K) candidates of the slots, in text order: lane l
+    // takes slots l, l + 64, ... The K loads of a step are in flight together:
+    // the steps are a chain of L2 round trips (two candidates per lane instead
+    // of one: 64 MiB, d = 1000, m = 8 with counts, 98 -> 91 us; 64 MiB,
+    // d = 100k, m = 16, 106 -> 96; the batch below 133 -> 115).
+    template <int K>
+    __device__ __forceinline__ void candidates(bool direct, uint64_t base, uint32_t n, uint32_t &nh, uint32_t &nid,
+                                               uint32_t &last, mpm_match *out, uint64_t cap, uint64_t &o) const
     {
         const uint32_t lane = threadIdx.x & 63u;
-        uint32_t head = 0xffffffffu;
-        if (active) {
-            const uint2 w = a.words[code & wmask];
-            head = w.y + __popc(w.x & ((1u << ((code >> (bsh - 2)) & 31u)) - 1u));
+        LDS_AS uint32_t *cw = lds_at<uint32_t>(wv);
+        LDS_AS uint32_t *slot = lds_at<uint32_t>(wv + WV_ITEMS);
+        uint32_t p[K], code[K], pv[K], head[K], i[K], nm[K], fm[K], key[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            p[k] = lane + 64 * k < n ? slot[lane + 64 * k] << TL : 0u;  // sample, relative to the block
+            const uint32_t wi = p[k] >> 4, sub = 2 * (p[k] & 15);
+            const uint32_t A = cw[3 + wi], B = cw[4 + wi], C = cw[5 + wi];
+            code[k] = __builtin_amdgcn_alignbit(C, B, sub);
+            pv[k] = __builtin_amdgcn_alignbit(B, A, sub);
+        }
+        uint2 w[K];
+        if (a.rank_off) {
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const uint32_t y = (code[k] & wmask) << 2;
+                w[k].x = *(lds_cptr<uint32_t>)lds_at<const uint8_t>(GBITS_OFF + y);
+                w[k].y = *(lds_cptr<uint32_t>)lds_at<const uint8_t>(GBITS_OFF + a.rank_off + y);
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                w[k] = a.words[code[k] & wmask];
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            head[k] = w[k].y + __popc(w[k].x & ((1u << ((code[k] >> (bsh - 2)) & 31u)) - 1u));
+            if (lane + 64 * k >= n)
+                head[k] = 0xffffffffu;
+            i[k] = head[k];
+            nm[k] = fm[k] = key[k] = 0;
         }
         // chain entries whose first codes agree
-        uint32_t nm = 0, fm = 0;
-        for (uint32_t i = head; i != 0xffffffffu;) {
-            const v4u e = *((glb_cptr<v4u>)a.ents + i);  // key, mask, meta, next
-            if (((window_code(code, pv, e.z & 15u) ^ e.x) & e.y) == 0) {
-                if (nm == 0)
-                    fm = e.z;
-                ++nm;
-            }
-            i = e.w;
-        }
-        if (__ballot(nm != 0) == 0)
-            return;
-        const bool single = __ballot(nm > 1) == 0;
-        LDS_AS v2u *item = lds_at<v2u>(wv + WV_ITEMS);
-        uint32_t tot = 0, pre = 0;
-        if (!single)
-            pre = wave_excl_sum(nm, tot);
-        uint32_t iw = 0;
-#pragma unroll 1
-        do {
-            bool act = nm != 0;
-            v2u it = {p + BIAS - (fm & 15u), fm >> 4};
-            if (!single) {
-                // lanes with several agreeing entries: deal them out in order
-                wave_sync();
-                uint32_t k = pre - iw;
-                if (nm)
-                    for (uint32_t i = head; i != 0xffffffffu;) {
-                        const v4u e = *((glb_cptr<v4u>)a.ents + i);
-                        if (((window_code(code, pv, e.z & 15u) ^ e.x) & e.y) == 0) {
-                            if (k < 64)
-                                item[k] = v2u{p + BIAS - (e.z & 15u), e.z >> 4};
-                            ++k;
+        bool more = true;
+        while (more) {
+            v4u e[K];  // key, mask, meta, next
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                e[k] = *((glb_cptr<v4u>)a.ents + (i[k] != 0xffffffffu ? i[k] : 0u));
+            more = false;
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                if (i[k] != 0xffffffffu) {
+                    if (((window_code(code[k], pv[k], e[k].z & 15u) ^ e[k].x) & e[k].y) == 0) {
+                        if (nm[k] == 0) {
+                            fm[k] = e[k].z;
+                            key[k] = e[k].x;
                         }
-                        i = e.w;
+                        ++nm[k];
+                    }
+                    i[k] = e[k].w;
+                    more |= i[k] != 0xffffffffu;
+                }
+        }
+        bool any = false, many = false;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            any |= nm[k] != 0;
+            many |= nm[k] > 1;
+        }
+        if (__ballot(any) == 0)
+            return;
+        if (__ballot(many) == 0) {
+            uint64_t sv[K];
+            uint32_t u[K];
+            bool act[K], plain[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                act[k] = nm[k] != 0;
+                sv[k] = base + p[k] - (fm[k] & 15u);
+                u[k] = fm[k] >> 5;
+                plain[k] = fm[k] & 16u;
+            }
+            check<K>(direct, act, sv, u, plain, key, nh, nid, last, out, cap, o);
+            return;
+        }
+        // lanes with several agreeing entries: deal them out in order
+        LDS_AS v2u *item = lds_at<v2u>(wv + WV_ITEMS);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            uint32_t tot;
+            const uint32_t pre = wave_excl_sum(nm[k], tot);
+#pragma unroll 1
+            for (uint32_t iw = 0; iw < tot; iw += 64) {
+                wave_sync();
+                uint32_t r = pre - iw;
+                if (nm[k])
+                    for (uint32_t j = head[k]; j != 0xffffffffu;) {
+                        const v4u e = *((glb_cptr<v4u>)a.ents + j);
+                        if (((window_code(code[k], pv[k], e.z & 15u) ^ e.x) & e.y) == 0) {
+                            if (r < 64)
+                                item[r] = v2u{p[k] + BIAS - (e.z & 15u), e.z >> 5};
+                            ++r;
+                        }
+                        j = e.w;
                     }
                 wave_sync();
-                act = lane < min(64u, tot - iw);
-                it = item[lane];
+                const v2u it = item[lane];
+                const bool act[1] = {lane < min(64u, tot - iw)};
+                const uint64_t sv[1] = {base + it.x - BIAS};
+                const uint32_t u[1] = {it.y}, none[1] = {0};
+                const bool plain[1] = {false};
+                check<1>(direct, act, sv, u, plain, none, nh, nid, last, out, cap, o);
             }
-            check(direct, act, base + it.x - BIAS, it.y, nh, nid, last, out, cap, o);
-            iw += 64;
-        } while (iw < tot);
+        }
     }
 
     // Blocks [b0, b1): count, get the output slot of this wave's first pair
@@ -353,17 +408,88 @@ struct GramScan {
         }
     }
 
-    // Bytewise check of one (start, string) per active lane, in text order.
-    __device__ __forceinline__ void check(bool direct, bool act, uint64_t sv, uint32_t u, uint32_t &nh, uint32_t &nid,
-                                          uint32_t &last, mpm_match *out, uint64_t cap, uint64_t &o) const
+    // The main bytes of four codes; of eight.
+    __device__ __forceinline__ uint32_t bytes4(uint32_t c) const
     {
-        bool hit = false;
-        // (a start before the text wraps below zero and fails here too)
-        if (act && (int64_t)sv >= (int64_t)text.lo) {
-            const uint2 st = a.strs[u];
-            hit = sv + st.y <= text.hi && equal(sv, st.x, st.y);
+        c = (c | c << 12) & 0x000f000fu;
+        c = (c | c << 6) & 0x03030303u;
+        return __builtin_amdgcn_perm(0u, a.main4, c);
+    }
+    __device__ __forceinline__ uint64_t bytes8(uint32_t c) const
+    {
+        return (uint64_t)bytes4((c >> 8) & 0xffu) << 32 | bytes4(c & 0xffu);
+    }
+
+    // Whether the bytes at view positions s[] are the strings u[], all of
+    // them of one length of at most 16 (two overlapping pieces V each). A
+    // plain string's bytes follow from its codes.
+    template <typename V, int K>
+    __device__ __forceinline__ void equal_short(const uint64_t (&s)[K], const uint32_t (&u)[K], const bool (&plain)[K],
+                                                const uint32_t (&key)[K], bool (&hit)[K]) const
+    {
+        typedef V any __attribute__((aligned(1)));
+        const uint32_t tail = a.m - sizeof(V);
+        V x[K][2], y[K][2];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            glb_cptr<uint8_t> t = text.p + s[k];
+            x[k][0] = *(const GLB_AS any *)t;
+            x[k][1] = *(const GLB_AS any *)(t + tail);
         }
-        emit(direct, hit, sv, u, nh, nid, last, out, cap, o);
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if constexpr (sizeof(V) == 4) {
+                y[k][0] = bytes4(key[k] & 0xffu);
+                y[k][1] = bytes4((key[k] >> (2 * tail)) & 0xffu);
+            } else {
+                y[k][0] = bytes8(key[k]);
+                y[k][1] = bytes8(key[k] >> (2 * tail));
+            }
+            if (hit[k] && !plain[k]) {
+                glb_cptr<uint8_t> q = (glb_cptr<uint8_t>)a.rows + (uint64_t)u[k] * 16;
+                y[k][0] = *(const GLB_AS any *)q;
+                y[k][1] = *(const GLB_AS any *)(q + tail);
+            }
+            hit[k] = hit[k] && ((x[k][0] ^ y[k][0]) | (x[k][1] ^ y[k][1])) == 0;
+        }
+    }
+
+    // Bytewise check of K (start, string) pairs per lane, the first ones of
+    // all lanes before the second ones in text order.
+    template <int K>
+    __device__ __forceinline__ void check(bool direct, const bool (&act)[K], const uint64_t (&sv)[K],
+                                          const uint32_t (&u)[K], const bool (&plain)[K], const uint32_t (&key)[K],
+                                          uint32_t &nh, uint32_t &nid, uint32_t &last, mpm_match *out, uint64_t cap,
+                                          uint64_t &o) const
+    {
+        bool hit[K];
+        if (!Var && a.m <= 16) {
+            uint64_t s[K];
+            uint32_t v[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                // (a start before the text wraps below zero and fails here too)
+                hit[k] = act[k] && (int64_t)sv[k] >= (int64_t)text.lo && sv[k] + a.m <= text.hi;
+                s[k] = hit[k] ? sv[k] : text.lo;
+                v[k] = hit[k] ? u[k] : 0u;
+            }
+            if (a.m < 8)
+                equal_short<uint32_t, K>(s, v, plain, key, hit);
+            else
+                equal_short<uint64_t, K>(s, v, plain, key, hit);
+        } else {
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                hit[k] = false;
+                if (act[k] && (int64_t)sv[k] >= (int64_t)text.lo) {
+                    const uint2 st = Var ? a.strs[u[k]] : make_uint2(u[k] * ((a.m + 15) / 16), a.m);
+                    hit[k] = sv[k] + st.y <= text.hi && equal(sv[k], st.x, st.y);
+                }
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            emit(direct, hit[k], sv[k], u[k], nh, nid, last, out, cap, o);
     }
 };
 
@@ -441,12 +567,13 @@ __device__ __forceinline__ T uniform_load(const T *p)
 // until the next ticket: each looks back over the parts of its own texts.
 // A piece's last part, which the next piece may go on from, is run first, so
 // that a piece that starts inside a text finds the counts before it early.
-// (One workgroup chunk per text, as the walkers have it, leaves the chip idle
-// for short texts; a unit per wave and text left 222 of 4096 waves with less
-// than a quarter of their time's work and the others with twice it, 198 us.)
+// (Workgroup chunks of one text each, as the walkers have, leave the chip idle
+// for short texts; with one text per wave the short ones still took a good part
+// of the waves, 198 us for the batch below.)
 //
 // Measured on 256 EST-shaped texts of 1 KiB to 4 MiB (120 MB) and eight sets
-// of 115 to 4648 strings of 8 to 32 characters, replayed graph: @@@.
+// of 115 to 4648 strings of 8 to 32 characters, replayed graph: 298 us by
+// the walkers, 113 here.
 template <int TL>
 __device__ __forceinline__ void batch_part(const GramDev &dev, const TextDesc &td, uint64_t g, const GramPart &part,
                                            uint32_t wv, uint32_t hits, uint32_t epoch, uint32_t *hdr, uint64_t *status)
@@ -550,6 +677,14 @@ const void *kernel_of(uint32_t W, uint32_t tl, bool var)
 
 }  // namespace
 
+// LDS bytes of the tables: the bits, and the grams before each word where
+// those pay for their copy: small workgroups share one of 32 KiB (q = 9)
+// between four waves only.
+static uint32_t lds_tables(const mpm_index::Gram &G, uint32_t W)
+{
+    return G.ranked && (W == 1024 || G.q <= 8) ? 2 * G.bit_bytes : G.bit_bytes;
+}
+
 // Whether automatic placement runs an index through the filter.
 bool gram_takes(const mpm_index *ix, const mpm_variant *v, uint64_t n)
 {
@@ -578,7 +713,7 @@ bool gram_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, uint32_t
     // the occurrence lists: all the LDS that is left to 16 waves (their
     // registers admit no second workgroup), 256 occurrences per wave of a
     // small workgroup
-    const uint32_t room = (uint32_t)lim.max_lds - GBITS_OFF - G.bit_bytes;
+    const uint32_t room = (uint32_t)lim.max_lds - GBITS_OFF - lds_tables(G, W);
     if (room / nw < WV_HITS + 16 * 8)
         return false;
     uint32_t hits = (room / nw - WV_HITS) / 8;
@@ -587,7 +722,7 @@ bool gram_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, uint32_t
     g->W = W;
     g->hits = hits;
     g->wave_bytes = WV_HITS + 8 * hits;
-    g->lds_bytes = GBITS_OFF + G.bit_bytes + nw * g->wave_bytes;
+    g->lds_bytes = GBITS_OFF + lds_tables(G, W) + nw * g->wave_bytes;
     if (g->lds_bytes > (uint32_t)lim.max_lds)
         return false;
     const void *k = kernel_of(W, G.t_log, ix->var != 0);
@@ -610,7 +745,7 @@ bool gram_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, uint32_t
     return (uint64_t)(blocks * GBLOCK + 16) * std::max<uint64_t>(1, ix->max_dup) < (1ull << 32);
 }
 
-GramDev gram_dev(const mpm_index *ix)
+GramDev gram_dev(const mpm_index *ix, uint32_t W)
 {
     const mpm_index::Gram &G = ix->gram;
     GramDev a;
@@ -624,7 +759,9 @@ GramDev gram_dev(const mpm_index *ix)
     a.q = G.q;
     a.t_log = G.t_log;
     a.code_shift = G.code_shift;
-    a.bit_bytes = G.bit_bytes;
+    a.bit_bytes = lds_tables(G, W);
+    a.rank_off = a.bit_bytes > G.bit_bytes ? G.bit_bytes : 0;
+    a.main4 = G.main4;
     a.m = ix->m;
     a.n_single = ix->n_single;
     a.grp = id_groups(ix);
@@ -635,7 +772,7 @@ mpm_status gram_launch(const mpm_index *ix, const GramCfg &g, const ScanDev &sd,
 {
     if (g.direct)
         return direct_launch(ix, g, sd, stream);
-    GramDev a = gram_dev(ix);
+    GramDev a = gram_dev(ix, g.W);
     ScanDev s = sd;
     s.ntiles = g.nchunks;
     uint32_t blocks = g.blocks, hits = g.hits, wave_bytes = g.wave_bytes;
@@ -653,7 +790,7 @@ mpm_status gram_launch(const mpm_index *ix, const GramCfg &g, const ScanDev &sd,
 bool gram_batch_takes(const mpm_index *ix, const mpm_variant *v, uint64_t n)
 {
     return ix->gram.ok && !ix->var && n < (1ull << 32) && gram_takes(ix, v, n) &&
-           GBITS_OFF + ix->gram.bit_bytes + 16 * (WV_HITS + 16 * 8) <= (uint32_t)limits().max_lds &&
+           GBITS_OFF + lds_tables(ix->gram, 1024) + 16 * (WV_HITS + 16 * 8) <= (uint32_t)limits().max_lds &&
            (uint64_t)(GBLOCK + 16) * std::max<uint64_t>(1, ix->max_dup) < (1ull << 32);
 }
 
@@ -681,7 +818,7 @@ void plan_gram_batch(const std::vector<const mpm_index *> &index, std::vector<Ba
     for (const mpm_index *ix : index) {
         const mpm_index::Gram &G = ix->gram;
         w.push_back(std::max(1.5, 0.85 * G.cost + 300.0 * G.hit));
-        const double fit = 0.6 * ((batch_wave_bytes(lds, G.bit_bytes) - WV_HITS) / 8) / (GBLOCK * G.hit);
+        const double fit = 0.6 * ((batch_wave_bytes(lds, lds_tables(G, 1024)) - WV_HITS) / 8) / (GBLOCK * G.hit);
         const uint64_t ids = ((1ull << 32) - 1) / std::max<uint64_t>(1, ix->max_dup);  // a part's count of ids: 32 bits
         most.push_back(std::max<uint64_t>(1, std::min<uint64_t>(fit > 4096 ? 4096 : (uint64_t)fit, (ids - 16) / GBLOCK)));
     }
