@@ -258,9 +258,10 @@ mpm_status mpm_workspace_bytes(const mpm_index *idx, uint64_t n, const mpm_varia
  * image, and MPM_PLACE_AUTO scans through it: every t-th position is looked
  * up in a bit table in LDS, and only text near a candidate is compared. Dense
  * sets of 2 to 8 characters keep a direct-address table instead: a window's
- * characters are the index of its ids. Both scans cut the text into chunks of their own, whatever lane_bytes and
- * block_threads say; a workspace smaller than mpm_workspace_bytes may make
- * the scan walk the tables instead. The list is the same.
+ * characters are the index of its ids. Both scans cut the text into chunks of
+ * their own, whatever lane_bytes and block_threads say; a workspace smaller
+ * than mpm_workspace_bytes may make the scan walk the tables instead. The list
+ * is the same.
  * Errors: EINVAL, ETOOBIG (n >= 2^32), ESTATE (index not uploaded), ENOMEM
  * (workspace too small), EHIP (launch failed). Device-side errors (a
  * look-back that never completes) set a flag read by mpm_scan_sync. */
@@ -371,6 +372,11 @@ typedef struct mpm_batch mpm_batch;
 /* Plan a batch: requests sharing (index, variant) are grouped into one
  * persistent launch whose workgroups take chunks of all the group's texts
  * from a shared ticket counter, each text keeping its own ordered output.
+ * Requests that mpm_scan would run through the q-gram filter (texts of 64
+ * bytes or more) form one launch of their own, whatever their indexes; its
+ * waves take pieces of equal expected time, of one or more texts. (With
+ * MPM_VARIANT_ILP2, which a batch otherwise ignores, a request stays with the
+ * walkers.)
  * The plan copies the request array. Host-only.
  * Errors: EINVAL, ETOOBIG, ENOMEM. */
 mpm_status mpm_batch_plan(const mpm_request *reqs, uint32_t count, mpm_batch **out);
@@ -394,7 +400,8 @@ uint32_t mpm_batch_groups(const mpm_batch *b);
 
 /* The launch a request with this index and variant joins in a plan: two
  * requests share a launch exactly when their keys are equal (walker kind,
- * block size, LDS class). Lets a caller predict a plan's launches while it
+ * block size, LDS class; one key for the q-gram filter, which texts below 64
+ * bytes do not join). Lets a caller predict a plan's launches while it
  * chooses variants; the value has no other meaning. Host-only.
  * Errors: EINVAL, EUNSUPPORTED (as mpm_batch_plan). */
 mpm_status mpm_batch_launch_key(const mpm_index *idx, const mpm_variant *variant, uint32_t *key);
