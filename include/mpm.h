@@ -251,7 +251,9 @@ mpm_status mpm_workspace_bytes(const mpm_index *idx, uint64_t n, const mpm_varia
  *             ready for the next scan. Scans that overlap in time must not
  *             share a workspace.
  *   d_total:  device uint64; receives the full number of pairs (may exceed
- *             capacity; the caller compares).
+ *             capacity; the caller compares). It may lie in the workspace, at
+ *             bytes 16 to 56, which no scan uses; mpm_scan_sync then reads it
+ *             back in one copy with the flags.
  *   v:        launch variant; NULL = defaults.
  * Sets whose strings rule out most of a text by a few characters (most sets
  * of 8 characters and more, either index kind) keep a q-gram filter in their

@@ -400,13 +400,12 @@ def scan(ix: Index, text, capacity: int | None = None, var: Variant | None = Non
     n = text.numel()
     cap = capacity if capacity is not None else n // 32 + 4096
     ws = new_workspace(ix, n, var, text.device)
-    total = torch.zeros(1, dtype=torch.int64, device=text.device)
     for _ in range(2):
         out = torch.empty((max(1, cap), 2), dtype=torch.int32, device=text.device)
         tot = C.c_uint64()
         st = _L.mpm_scan_sync(ix.handle, C.c_void_p(text.data_ptr()), n,
                               C.c_void_p(out.data_ptr()), cap, C.c_void_p(ws.data_ptr()),
-                              ws.numel() * 8, C.c_void_p(total.data_ptr()),
+                              ws.numel() * 8, C.c_void_p(ws.data_ptr() + 16),  # header word no scan uses
                               C.byref(var) if var else None, _stream_handle(stream), C.byref(tot))
         if st == MPM_EOVERFLOW and capacity is None:
             cap = int(tot.value)

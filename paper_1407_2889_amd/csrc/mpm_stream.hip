@@ -12,6 +12,8 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <mutex>
+#include <vector>
 
 #include "mpm_internal.h"
 
@@ -26,19 +28,76 @@ __global__ void add_base_kernel(uint32_t *__restrict__ pairs, uint64_t count, ui
         pairs[2 * i] += base;
 }
 
-// Copy stream and events of one call, released on every exit path.
+// Copy stream and events of a call.
 struct StreamSet {
+    int dev = -1;
     hipStream_t copy = nullptr;
     hipEvent_t ready[2] = {nullptr, nullptr};
-    ~StreamSet()
+    bool make()
     {
-        if (copy) {
-            (void)hipStreamSynchronize(copy);
+        return hipGetDevice(&dev) == hipSuccess &&
+               hipStreamCreateWithFlags(&copy, hipStreamNonBlocking) == hipSuccess &&
+               hipEventCreateWithFlags(&ready[0], hipEventDisableTiming) == hipSuccess &&
+               hipEventCreateWithFlags(&ready[1], hipEventDisableTiming) == hipSuccess;
+    }
+    void destroy()
+    {
+        if (copy)
             (void)hipStreamDestroy(copy);
-        }
         for (hipEvent_t e : ready)
             if (e)
                 (void)hipEventDestroy(e);
+    }
+};
+
+// A call's set, given back on every exit path once its copies are done. Up to
+// KEEP idle sets are kept (64 MiB of text in four chunks, with the totals read
+// back through pinned memory: 1472 us when each call made its own, 1348 here;
+// the four copies alone 1205).
+class StreamLease {
+public:
+    bool take()
+    {
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess)
+            return false;
+        Pool &p = pool();
+        {
+            std::lock_guard<std::mutex> g(p.mu);
+            for (size_t i = 0; i < p.idle.size(); i++)
+                if (p.idle[i].dev == dev) {
+                    set = p.idle[i];
+                    p.idle.erase(p.idle.begin() + i);
+                    return true;
+                }
+        }
+        return set.make();
+    }
+    ~StreamLease()
+    {
+        if (set.copy && hipStreamSynchronize(set.copy) == hipSuccess && set.ready[1]) {
+            Pool &p = pool();
+            std::lock_guard<std::mutex> g(p.mu);
+            if (p.idle.size() < KEEP) {
+                p.idle.push_back(set);
+                return;
+            }
+        }
+        set.destroy();
+    }
+    StreamSet set;
+
+private:
+    static const size_t KEEP = 8;
+    struct Pool {
+        std::mutex mu;
+        std::vector<StreamSet> idle;
+        Pool() { idle.reserve(KEEP); }
+    };
+    static Pool &pool()
+    {
+        static Pool *const p = new Pool;  // lives as long as the process
+        return *p;
     }
 };
 
@@ -79,11 +138,10 @@ extern "C" mpm_status mpm_scan_host(const mpm_index *idx, const uint8_t *h_text,
         return fail(MPM_ENOMEM, "mpm_scan_host: staging buffer of %llu bytes, need %llu",
                     (unsigned long long)stage_bytes,
                     (unsigned long long)((nchunks > 1 ? 2 : 1) * buf_bytes));
-    StreamSet ss;
-    if (hipStreamCreateWithFlags(&ss.copy, hipStreamNonBlocking) != hipSuccess ||
-        hipEventCreateWithFlags(&ss.ready[0], hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&ss.ready[1], hipEventDisableTiming) != hipSuccess)
+    StreamLease lease;
+    if (!lease.take())
         return fail(MPM_EHIP, "mpm_scan_host: stream or event creation failed");
+    const StreamSet &ss = lease.set;
     // Byte range of chunk k: its starting positions and the m - 1 bytes after them.
     auto bytes_of = [&](uint64_t k) { return std::min(n, (k + 1) * chunk + m - 1) - k * chunk; };
     auto copy = [&](uint64_t k) -> hipError_t {
