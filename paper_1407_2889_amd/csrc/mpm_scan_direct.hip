@@ -23,11 +23,14 @@
 // over the same codes, and windows that pass it are compared byte by byte.
 //
 // Measured against the dense-output walkers (EST-shaped text, m = 8, us, before
-// and after): 64 MiB, d = 10k 396 -> 189, d = 100k (92 M pairs) 855 -> 388;
-// 4 MiB, d = 100k 67 -> 46. A round of 256 positions takes about 0.9 us
-// (60 us of the 64 MiB scan) plus what its pairs take to gather and write;
-// keeping the first pass's strings in registers (64 unrolled rounds) or their
-// id counts as scalar thresholds measured 586 to 860 us for d = 100k.
+// and after): 64 MiB, d = 10k 398 -> 189, d = 100k (92 M pairs) 856 -> 368;
+// 16 MiB, d = 30k 492 -> 65; 4 MiB, d = 30k 133 -> 39. Vector issue bounds it:
+// sixteen waves of a CU share four SIMDs, an instruction takes one of them four
+// cycles, and a round of 256 positions has 200 to 300, besides what its pairs
+// take to gather and write (d = 100k with odd strings looked up round by round,
+// four runs of ids in flight and branches around each item: 390). Keeping the
+// first pass's strings in registers (64 unrolled rounds) or their id counts as
+// scalar thresholds measured 586 to 860 us for d = 100k.
 #include "mpm_gram.h"
 
 namespace mpm {
@@ -39,12 +42,14 @@ static_assert(1024 / 64 * DBLOCK >> 4 >= GRAM_CHUNK_MIN, "workspace bound");
 constexpr uint32_t DTAB_OFF = LDS_CLS_OFF;
 // One wave's LDS: code words (from [4] on the block, [260] the 16 characters
 // after it); a bit per position that takes its ids from the table; a bit per
-// odd window; the items of a round.
+// odd window that may be an odd string; the items of a round; the block's odd
+// strings (position, first id, number of ids).
 constexpr uint32_t DW_KEEP = 264 * 4;
 constexpr uint32_t DW_ODD = DW_KEEP + 512;
 constexpr uint32_t DW_ITEMS = DW_ODD + 512;
 constexpr uint32_t DITEMS = 512;
-constexpr uint32_t DW_BYTES = DW_ITEMS + 4 * DITEMS;
+constexpr uint32_t DW_LIST = DW_ITEMS + 4 * (DITEMS + 64);
+constexpr uint32_t DW_BYTES = DW_LIST + 3 * 64 * 4;
 
 // Bit per byte of c that is not the main byte of its code.
 __device__ __forceinline__ uint32_t odd4(uint32_t w, uint32_t sh, uint32_t main4)
@@ -92,6 +97,42 @@ struct DirectScan {
     __device__ __forceinline__ bool odd_bit(uint32_t code) const
     {
         return lds_at<const uint32_t>(obits)[code >> 5] >> (code & 31u) & 1u;
+    }
+
+    // Of a block's odd windows (one bit per position of the lane) those with an
+    // odd string's codes, for the whole wave: few, so that they are looked up
+    // together, 64 at a time, found(position, s, n) per lane. Returns the bits,
+    // tot their number.
+    template <class F>
+    __device__ __forceinline__ uint64_t odd_windows(uint64_t vb, uint64_t odd, uint32_t &tot, F found) const
+    {
+        const uint32_t lane = threadIdx.x & 63u;
+        LDS_AS uint32_t *cw = lds_at<uint32_t>(wv);
+        LDS_AS uint32_t *list = lds_at<uint32_t>(wv + DW_LIST);
+        uint64_t hit = 0;
+        for (uint64_t q = odd; q; q &= q - 1) {
+            const uint32_t j = (uint32_t)__builtin_ctzll(q), wi = 4 + 4 * lane + (j >> 4);
+            if (odd_bit(__builtin_amdgcn_alignbit(cw[wi + 1], cw[wi], 2 * (j & 15u)) & cmask()))
+                hit |= 1ull << j;
+        }
+        const uint32_t mine = (uint32_t)__popcll(hit), incl = wave_incl_sum(mine);
+        tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+#pragma unroll 1
+        for (uint32_t win = 0; win < tot; win += 64) {
+            wave_sync();
+            uint32_t at = incl - mine - win;  // below 64: this window's place
+            for (uint64_t q = hit; q; q &= q - 1, ++at)
+                if (at < 64)
+                    list[at] = 64 * lane + (uint32_t)__builtin_ctzll(q);
+            wave_sync();
+            if (lane < tot - win) {
+                const uint32_t p = list[lane], wi = 4 + (p >> 4);
+                uint32_t s = 0, n = 0;
+                odd_string(vb + p, __builtin_amdgcn_alignbit(cw[wi + 1], cw[wi], 2 * (p & 15u)) & cmask(), s, n);
+                found(p, s, n);
+            }
+        }
+        return hit;
     }
 
     // Units [u0, u1) of a wave: unit u is part u mod 2^split of block
@@ -181,20 +222,12 @@ struct DirectScan {
                 const uint32_t x = sub ? __builtin_amdgcn_alignbit(c[k + 1], c[k], sub) : c[k];
                 const uint32_t w = *(lds_cptr<uint32_t>)lds_at<const uint8_t>(DTAB_OFF + ((x >> 1) & amask));
                 const uint32_t kh = s < 32 ? (uint32_t)keep : (uint32_t)(keep >> 32);
-                sum += __builtin_amdgcn_ubfe(w, x << 2, 4) & (uint32_t)__builtin_amdgcn_sbfe((int)kh, s & 31, 1);
+                sum = __umul24(__builtin_amdgcn_ubfe(w, x << 2, 4), __builtin_amdgcn_ubfe(kh, s & 31, 1)) + sum;
             }
             if (a.odd_bytes) {
                 wave_sync();
-                LDS_AS uint32_t *cw = lds_at<uint32_t>(wv);
-                for (uint64_t q = odd; q; q &= q - 1) {
-                    const uint32_t j = (uint32_t)__builtin_ctzll(q), wi = 4 + 4 * lane + (j >> 4);
-                    const uint32_t code = __builtin_amdgcn_alignbit(cw[wi + 1], cw[wi], 2 * (j & 15u)) & cmask();
-                    if (odd_bit(code)) {
-                        uint32_t s0, n = 0;
-                        odd_string(vb + lane * 64 + j, code, s0, n);
-                        sum += n;
-                    }
-                }
+                uint32_t tot;
+                (void)odd_windows(vb, odd, tot, [&](uint32_t, uint32_t, uint32_t n) { sum += n; });
             }
         }
         return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_sum(sum), 63);
@@ -202,12 +235,33 @@ struct DirectScan {
 
     __device__ __forceinline__ uint32_t cmask() const { return (1u << (2 * a.m)) - 1u; }
 
+    // The pairs of a round's first `many` <= 64 K items.
+    template <int K>
+    __device__ __forceinline__ static void write_items(GLB_AS v2u *at, LDS_AS uint32_t *item, glb_cptr<uint32_t> ids,
+                                                       uint32_t many, uint32_t pos)
+    {
+        const uint32_t lane = threadIdx.x & 63u;
+        // (the last lanes of the last run write the last pair again)
+        uint32_t it[K], id[K], at_[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            at_[k] = min(lane + 64 * k, many - 1);
+            it[k] = item[at_[k]];
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            id[k] = ids[it[k] >> 8];
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            at[at_[k]] = v2u{pos + (it[k] & 255u), id[k]};
+    }
+
     // The pairs of units [b0, b1) from output slot o on.
     __device__ __forceinline__ void write(uint64_t b0, uint64_t b1, mpm_match *out_, uint64_t cap, uint64_t o) const
     {
         const uint32_t lane = threadIdx.x & 63u;
         LDS_AS uint32_t *cw = lds_at<uint32_t>(wv);
-        LDS_AS uint32_t *item = lds_at<uint32_t>(wv + DW_ITEMS);
+        LDS_AS uint32_t *item = lds_at<uint32_t>(wv + DW_ITEMS), *list = lds_at<uint32_t>(wv + DW_LIST);
         GLB_AS v2u *out = (GLB_AS v2u *)out_;
         glb_cptr<uint32_t> ids = (glb_cptr<uint32_t>)a.ids;
         v4u r[4];
@@ -219,8 +273,18 @@ struct DirectScan {
             block(vb, r, c, keep, odd);
             if (b + 1 < b1)
                 T.load(((b + 1) >> split) * DBLOCK, lane, r);
+            // the block's odd strings; more than the list holds are looked up
+            // again where they are needed
+            uint32_t nodd = 0;
+            if (a.odd_bytes) {
+                wave_sync();
+                odd = odd_windows(vb, in_part(b, lane) ? odd : 0, nodd, [&](uint32_t, uint32_t s, uint32_t n) {
+                    list[64 + lane] = s;
+                    list[128 + lane] = n;
+                });
+                lds_at<uint64_t>(wv + DW_ODD)[lane] = odd;
+            }
             lds_at<uint64_t>(wv + DW_KEEP)[lane] = keep;
-            lds_at<uint64_t>(wv + DW_ODD)[lane] = odd;
             wave_sync();
 #pragma unroll 1
             for (uint32_t i = ((uint32_t)b & ((1u << split) - 1u)) << (4 - split), e = i + (16u >> split); i < e; ++i) {
@@ -239,14 +303,24 @@ struct DirectScan {
                     s[k] = __builtin_amdgcn_udot8(w & ((1u << f) - 1u), 0x11111111u, base, false);
                     n[k] = __builtin_amdgcn_ubfe(w, f, 4) & (uint32_t)__builtin_amdgcn_sbfe((int)kp, k, 1);
                 }
-                if (a.odd_bytes) {
+                if (nodd) {
                     const uint32_t od = ((uint32_t)lds_at<const uint8_t>(wv + DW_ODD)[bit] >> nb) & 15u;
                     if (__ballot(od != 0)) {
+                        if (nodd <= 64) {
+                            for (uint32_t j = 0; j < nodd; ++j) {
+                                const uint32_t rel = list[j] - (256 * i + 4 * lane);
 #pragma unroll
-                        for (uint32_t k = 0; k < 4; ++k) {
-                            const uint32_t code = (x >> (2 * k)) & cmask();
-                            if ((od >> k & 1u) && odd_bit(code))
-                                odd_string(vb + 256 * i + 4 * lane + k, code, s[k], n[k]);
+                                for (uint32_t k = 0; k < 4; ++k)
+                                    if (rel == k) {
+                                        s[k] = list[64 + j];
+                                        n[k] = list[128 + j];
+                                    }
+                            }
+                        } else {
+#pragma unroll
+                            for (uint32_t k = 0; k < 4; ++k)
+                                if (od >> k & 1u)
+                                    odd_string(vb + 256 * i + 4 * lane + k, (x >> (2 * k)) & cmask(), s[k], n[k]);
                         }
                     }
                 }
@@ -261,11 +335,11 @@ struct DirectScan {
                     if (total <= DITEMS) {
 #pragma unroll
                         for (uint32_t k = 0; k < 4; ++k) {
+                            // (lanes without an item write to a spare slot:
+                            // a select costs less than a branch)
                             const uint32_t v = s[k] << 8 | (4 * lane + k);
-                            if (n[k] > 0)
-                                item[q] = v;
-                            if (n[k] > 1)
-                                item[q + 1] = v + 256;
+                            item[n[k] > 0 ? q : DITEMS + lane] = v;
+                            item[n[k] > 1 ? q + 1 : DITEMS + lane] = v + 256;
                             if (deep)
                                 for (uint32_t t = 2; t < n[k]; ++t)
                                     item[q + t] = v + 256 * t;
@@ -283,21 +357,15 @@ struct DirectScan {
                     const uint64_t room = cap - o > win ? cap - o - win : 0;
                     const uint32_t many = (uint32_t)min((uint64_t)min(total - win, DITEMS), room);
                     GLB_AS v2u *at = out + o + win;
-#pragma unroll 1
-                    for (uint32_t j = lane; j < many + lane; j += 64 * 4) {
-                        // the ids of four runs of 64 pairs requested together
-                        uint32_t it[4], id[4];
-#pragma unroll
-                        for (uint32_t k = 0; k < 4; ++k)
-                            it[k] = j + 64 * k < many ? item[j + 64 * k] : 0u;
-#pragma unroll
-                        for (uint32_t k = 0; k < 4; ++k)
-                            id[k] = ids[it[k] >> 8];
-#pragma unroll
-                        for (uint32_t k = 0; k < 4; ++k)
-                            if (j + 64 * k < many)
-                                at[j + 64 * k] = v2u{pos + (it[k] & 255u), id[k]};
-                    }
+                    // the ids of all runs of 64 pairs requested together
+                    if (many > 384)
+                        write_items<8>(at, item, ids, many, pos);
+                    else if (many > 256)
+                        write_items<6>(at, item, ids, many, pos);
+                    else if (many > 128)
+                        write_items<4>(at, item, ids, many, pos);
+                    else if (many)
+                        write_items<2>(at, item, ids, many, pos);
                 }
                 o += total;
                 if (o >= cap)
