@@ -158,6 +158,13 @@ double cost_of(uint32_t q, uint32_t t, double cand, double steps)
     return (1.2 + 6.0 / t + 120.0 * cand + 20.0 * steps) * (q == Q_MAX ? 1.25 : 1.0);
 }
 
+// What a candidate costs more when the entries (16 bytes for each string and
+// offset) outgrow the 4 MB L2 of an XCD, which they share with the text:
+// 64 MiB, d = 100k, m = 32, q = 10, entries of 1.6, 3.2, 6.4, 12.8, 25.6 MB
+// (t = 1 to 16): 97, 95, 105, 120, 132 us, for 0.091 to 0.049 candidates per
+// byte.
+double spread_of(uint32_t t, uint32_t du) { return pow(std::max(1.0, 16.0 * t * du / 3.4e6), 0.63); }
+
 }  // namespace
 
 // Choose q and t, and append the tables to the index's device image; leaves
@@ -172,9 +179,10 @@ void build_gram(mpm_index *ix)
     double freq[256], share[4];
     const uint32_t sh = code_shift_of(ix->upats, freq, share);
     // The cheapest (t, q), by the cost if grams were spread evenly; the first
-    // few are then counted.
+    // few are then counted. (The spread of the entries decides between them
+    // alone: the limits on the cost stand for what a candidate costs in L2.)
     struct Choice {
-        double cost;
+        double cost, plain;  // with and without the spread
         uint32_t tl, q;
     };
     std::vector<Choice> all;
@@ -182,22 +190,26 @@ void build_gram(mpm_index *ix)
         const uint32_t t = 1u << tl;
         for (uint32_t q = 4; q <= Q_MAX && q + t - 1 <= m; q++) {
             const double even = (double)ix->du / (double)(1ull << (2 * q));
-            all.push_back({cost_of(q, t, (1.0 - exp(-even * t)) / t, even), tl, q});
+            const double cand = (1.0 - exp(-even * t)) / t;
+            all.push_back({cost_of(q, t, cand * spread_of(t, ix->du), even), cost_of(q, t, cand, even), tl, q});
         }
     }
     std::stable_sort(all.begin(), all.end(), [](const Choice &x, const Choice &y) { return x.cost < y.cost; });
     const std::vector<uint64_t> head = head_codes(ix, S, sh);
     std::vector<uint8_t> count;
-    double best = 1e300, cand = 0;
+    double best = 1e300, chosen = 1e300;
     uint32_t bq = 0, bt = 0;
-    for (size_t k = 0; k < all.size() && k < 4 && all[k].cost < std::min(0.9 * best, 25.0); k++) {
-        const Rate r = rate_of(head, all[k].q, 1u << all[k].tl, share, count);
+    for (size_t k = 0; k < all.size() && k < 4 && (all[k].cost < 0.9 * chosen || best > 25.0); k++) {
+        if (all[k].plain >= 25.0)
+            continue;
+        const uint32_t tk = 1u << all[k].tl;
+        const Rate r = rate_of(head, all[k].q, tk, share, count);
         if (r.longest > CHAIN_MAX)
             continue;
-        const double c = cost_of(all[k].q, 1u << all[k].tl, r.cand, r.steps);
-        if (c < best) {
-            best = c;
-            cand = r.cand;
+        best = std::min(best, cost_of(all[k].q, tk, r.cand, r.steps));
+        const double c = cost_of(all[k].q, tk, r.cand * spread_of(tk, ix->du), r.steps);
+        if (c < chosen) {
+            chosen = c;
             bq = all[k].q;
             bt = all[k].tl;
         }
