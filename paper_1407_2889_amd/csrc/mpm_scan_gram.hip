@@ -238,17 +238,16 @@ struct GramScan {
                 cw[3] = before;
                 cw[4 + 64 * GN] = ct;
             }
-            uint32_t tot;
-            const uint32_t pre = wave_excl_sum(cnt, tot);
+            const uint32_t incl = wave_incl_sum(cnt);
+            const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+            uint32_t rk = incl - cnt;  // place of the lane's next candidate
 #pragma unroll 1
             for (uint32_t win = 0; win < tot; win += 128) {
                 wave_sync();
-                uint32_t rk = pre - win;  // below 128: this window's slot
 #pragma unroll
                 for (uint32_t h = 0; h < NM; ++h)
-                    for (uint32_t mm = mk[h]; mm; mm &= mm - 1, ++rk)
-                        if (rk < 128)
-                            slot[rk] = lane * NS + 32 * h + (uint32_t)__builtin_ctz(mm);
+                    for (; mk[h] && rk < win + 128; mk[h] &= mk[h] - 1, ++rk)
+                        slot[rk - win] = lane * NS + 32 * h + (uint32_t)__builtin_ctz(mk[h]);
                 wave_sync();
                 if (tot - win > 64)
                     candidates<2>(direct, b * GBLOCK, tot - win, nh, nid, last, out, cap, o);
