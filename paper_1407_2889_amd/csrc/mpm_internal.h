@@ -388,9 +388,21 @@ mpm_status var_launch(const mpm_index *ix, const LaunchCfg &c, const ScanDev &sd
 const void *ladder_kernel(const mpm_index *ix, const LaunchCfg &c);
 mpm_status ladder_launch(const mpm_index *ix, const LaunchCfg &c, const ScanDev &sd, void *stream);
 // q-gram filter scans (mpm_gram.cpp, mpm_scan_gram.hip).
+// Items (text blocks) of wave k, of a number of waves that the items are spread
+// over evenly: [first(k), first(k + 1)). frac is the remainder's share in
+// units of 2^-32, rounded up: first(waves) is the number of items.
+struct GramShare {
+    uint32_t per, frac;
+    __host__ __device__ uint64_t first(uint64_t k) const { return k * per + (k * frac >> 32); }
+};
+inline GramShare gram_share(uint64_t items, uint64_t waves)
+{
+    const uint64_t rem = items % waves;
+    return GramShare{(uint32_t)(items / waves), rem ? (uint32_t)((rem << 32) / waves + 1) : 0u};
+}
 struct GramCfg {
     uint32_t W;            // threads per workgroup
-    uint32_t blocks;       // text blocks per wave and chunk
+    GramShare share;       // of the waves of all chunks
     uint32_t grid;
     uint32_t lds_bytes;
     uint32_t wave_bytes;   // LDS bytes of one wave's buffers

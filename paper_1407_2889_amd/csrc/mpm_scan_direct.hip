@@ -376,8 +376,7 @@ struct DirectScan {
 };
 
 constexpr int W = 1024;
-__global__ __launch_bounds__(W) void direct_kernel(DirectDev a, ScanDev sd, uint32_t units, uint64_t nunits,
-                                                   uint32_t split)
+__global__ __launch_bounds__(W) void direct_kernel(DirectDev a, ScanDev sd, GramShare share, uint32_t split)
 {
     extern __shared__ __align__(16) uint8_t smem[];
     if (!lds_layout_ok(smem, sd.hdr))
@@ -413,8 +412,7 @@ __global__ __launch_bounds__(W) void direct_kernel(DirectDev a, ScanDev sd, uint
         const uint64_t g = uniform64(s_tile);
         if (g >= sd.ntiles)
             break;
-        const uint64_t b0 = min((g * NW + wave) * units, nunits);
-        const uint64_t b1 = min(b0 + units, nunits);
+        const uint64_t b0 = share.first(g * NW + wave), b1 = share.first(g * NW + wave + 1);
         const uint32_t n = sc.count(hidden(b0), b1);
         const uint64_t o = wave_offset<W>(n, s_scan, sd.status, g, sd.ntiles, sd.single.total, s_epoch | GRAM_EPOCH,
                                           &hdr[WS_ERR]);
@@ -464,8 +462,9 @@ bool direct_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, uint32
         nb = 1;
     const uint64_t slots = (uint64_t)nb * lim.cus;
     const uint64_t units = std::min<uint64_t>(256, (g->nblocks + slots * nw - 1) / (slots * nw));
-    g->blocks = (uint32_t)units;
     g->nchunks = (g->nblocks + units * nw - 1) / (units * nw);
+    g->nchunks = std::min((g->nchunks + slots - 1) / slots * slots, (g->nblocks + nw - 1) / nw);
+    g->share = gram_share(g->nblocks, g->nchunks * nw);
     const uint64_t grid = v && v->grid ? v->grid : slots;
     g->grid = (uint32_t)std::max<uint64_t>(1, std::min(grid, g->nchunks));
     // a wave's count of ids stays in 32 bits
@@ -490,9 +489,9 @@ mpm_status direct_launch(const mpm_index *ix, const GramCfg &g, const ScanDev &s
     a.main4 = D.main4;
     ScanDev s = sd;
     s.ntiles = g.nchunks;
-    uint32_t units = g.blocks, split = g.split;
-    uint64_t nunits = g.nblocks;
-    void *args[] = {&a, &s, &units, &nunits, &split};
+    GramShare share = g.share;
+    uint32_t split = g.split;
+    void *args[] = {&a, &s, &share, &split};
     const hipError_t e = hipLaunchKernel((const void *)direct_kernel, dim3(g.grid), dim3(g.W), args, g.lds_bytes,
                                          (hipStream_t)stream);
     if (e != hipSuccess)

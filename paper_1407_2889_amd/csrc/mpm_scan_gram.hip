@@ -28,10 +28,11 @@
 // (t = 8, q = 9, one candidate per 260 bytes) that is below what HBM asks for.
 //
 // Measured (EST-shaped text, walkers before, filter after, us): 256 MiB,
-// d = 1000, m = 16: AC 102 -> 63, WM 99 -> 63 (4.2 TB/s of text); 128 MiB,
-// d = 10k, m = 16, AC 366 -> 48; 64 MiB, d = 100k, m = 16, WM 3577 -> 97;
-// 64 MiB, d = 1000, m = 8 with counts, WM 422 -> 91; 128 MiB, lengths 8-32,
-// AC 135 -> 67; 32 MiB, lengths 8-32, WM 2132 -> 31.
+// d = 1000, m = 16: AC 102 -> 62.6, WM 99 -> 62.5 (4.3 TB/s of text; while all
+// waves stream, 6.3 TB/s: the rest is the start and the wait for the slowest
+// wave); 128 MiB, d = 10k, m = 16, AC 366 -> 49; 64 MiB, d = 100k, m = 16, WM
+// 3554 -> 75; 64 MiB, d = 1000, m = 8 with counts, WM 421 -> 75; 128 MiB,
+// lengths 8-32, AC 134 -> 66; 32 MiB, lengths 8-32, WM 2110 -> 27.
 #include "mpm_gram.h"
 
 #include <cmath>
@@ -493,8 +494,8 @@ struct GramScan {
 };
 
 template <int W, int TL, bool Var>
-__global__ __launch_bounds__(W) void gram_kernel(GramDev a, ScanDev sd, uint32_t blocks, uint64_t nblocks,
-                                                 uint32_t hits, uint32_t wave_bytes)
+__global__ __launch_bounds__(W) void gram_kernel(GramDev a, ScanDev sd, GramShare share, uint32_t hits,
+                                                 uint32_t wave_bytes)
 {
     extern __shared__ __align__(16) uint8_t smem[];
     if (!lds_layout_ok(smem, sd.hdr))
@@ -526,8 +527,7 @@ __global__ __launch_bounds__(W) void gram_kernel(GramDev a, ScanDev sd, uint32_t
         const uint64_t g = uniform64(s_tile);
         if (g >= ntiles)
             break;
-        const uint64_t b0 = min((g * NW + wave) * blocks, nblocks);
-        const uint64_t b1 = min(b0 + blocks, nblocks);
+        const uint64_t b0 = share.first(g * NW + wave), b1 = share.first(g * NW + wave + 1);
         sc.part(b0, b1, sd.single.out, cap, [&](uint32_t nid) {
             return wave_offset<W>(nid, s_scan, sd.status, g, ntiles, sd.single.total, s_epoch | GRAM_EPOCH,
                                   &hdr[WS_ERR]);
@@ -572,7 +572,7 @@ __device__ __forceinline__ T uniform_load(const T *p)
 //
 // Measured on 256 EST-shaped texts of 1 KiB to 4 MiB (120 MB) and eight sets
 // of 115 to 4648 strings of 8 to 32 characters, replayed graph: 298 us by
-// the walkers, 113 here.
+// the walkers, 106 here.
 template <int TL>
 __device__ __forceinline__ void batch_part(const GramDev &dev, const TextDesc &td, uint64_t g, const GramPart &part,
                                            uint32_t wv, uint32_t hits, uint32_t epoch, uint32_t *hdr, uint64_t *status)
@@ -736,8 +736,12 @@ bool gram_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, uint32_t
     uint64_t blocks = (nblocks + slots * nw - 1) / (slots * nw);
     const double fit = 0.6 * hits / (GBLOCK * G.hit);
     blocks = std::max<uint64_t>(1, std::min<uint64_t>(blocks, fit > 4096 ? 4096 : (uint64_t)fit));
-    g->blocks = (uint32_t)blocks;
+    // The blocks are spread evenly over whole rounds of chunks (64 MiB and
+    // 12 KB, 4.001 blocks per wave, d = 100k, m = 16: 80.4 us when 3,278 waves
+    // took five each, 75.0 now; 32 MiB and 7 bytes, lengths 8-32: 29.9 -> 26.9).
     g->nchunks = (nblocks + blocks * nw - 1) / (blocks * nw);
+    g->nchunks = std::min((g->nchunks + slots - 1) / slots * slots, (nblocks + nw - 1) / nw);
+    g->share = gram_share(nblocks, g->nchunks * nw);
     uint64_t grid = v && v->grid ? v->grid : slots;
     g->grid = (uint32_t)std::max<uint64_t>(1, std::min(grid, g->nchunks));
     // a wave's count of ids stays in 32 bits
@@ -774,9 +778,9 @@ mpm_status gram_launch(const mpm_index *ix, const GramCfg &g, const ScanDev &sd,
     GramDev a = gram_dev(ix, g.W);
     ScanDev s = sd;
     s.ntiles = g.nchunks;
-    uint32_t blocks = g.blocks, hits = g.hits, wave_bytes = g.wave_bytes;
-    uint64_t nblocks = g.nblocks;
-    void *args[] = {&a, &s, &blocks, &nblocks, &hits, &wave_bytes};
+    GramShare share = g.share;
+    uint32_t hits = g.hits, wave_bytes = g.wave_bytes;
+    void *args[] = {&a, &s, &share, &hits, &wave_bytes};
     const hipError_t e = hipLaunchKernel(kernel_of(g.W, ix->gram.t_log, ix->var != 0), dim3(g.grid), dim3(g.W),
                                          args, g.lds_bytes, (hipStream_t)stream);
     if (e != hipSuccess)
