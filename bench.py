@@ -49,8 +49,8 @@ METRIC = "text GB/s scanned (AC, WM) + %HBM roofline; learned vs exhaustive-tune
 
 # The sources the single-text AC and WM scan kernels and their launches are
 # built from (the kernels' template code, its launch and workspace set-up).
-SCAN_SOURCES = ("mpm_internal.h", "mpm_scan_impl.h", "mpm_scan.hip", "mpm_scan_ac16_lds.hip",
-                "mpm_scan_wm.hip", "mpm_host.cpp")
+SCAN_SOURCES = ("mpm_internal.h", "mpm_scan_impl.h", "mpm_gram.h", "mpm_gram.cpp", "mpm_scan_gram.hip",
+                "mpm_host.cpp")
 
 
 def kernel_digest() -> str:
@@ -802,7 +802,7 @@ def main():
         "index_build_s": round(build_s, 3),
         "hbm_read_ceiling_gbs": round(read_ceiling, 1),
         "frac_of_read_ceiling": {k: round(gbs[k] / read_ceiling, 4) for k in ("ac", "wm")},
-        "roofline": {"bound": "hbm", "kernel": f"scan_kernel ({dom.upper()})",
+        "roofline": {"bound": "hbm", "kernel": f"scan ({dom.upper()})",
                      "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": recorded_traffic(args.workload, dom),
