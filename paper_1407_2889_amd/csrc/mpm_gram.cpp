@@ -281,7 +281,7 @@ void build_gram(mpm_index *ix)
         rows.insert(rows.end(), S.at(u), S.at(u) + S.len(u));
         rows.resize((rows.size() + 15) / 16 * 16, 0);
     }
-    ix->image.reserve(ix->image.size() + 4ull * (bits.size() + 2 * words.size() + 4 * ents.size() + 2 * strs.size()) +
+    ix->image.reserve(ix->image.size() + 4ull * (2 * bits.size() + 4 * ents.size() + 2 * strs.size()) +
                       rows.size() + 2048);
     G.q = q;
     G.cost = best;
@@ -296,16 +296,14 @@ void build_gram(mpm_index *ix)
     G.code_shift = sh;
     memcpy(&G.main4, main4, 4);
     G.bit_bytes = nw * 4;
-    // Where they fit beside the bits the grams before each word are copied to
-    // LDS too: a candidate then finds its entry without a load from `words`
+    // Behind the bits the grams before each word. Where they fit beside the bits
+    // in LDS they are copied too: a candidate then finds its entry without a load
     // (256 MiB, d = 1000, m = 16: 68.3 -> 63.2 us; 128 MiB, lengths 8-32:
     // 69.8 -> 67.0).
     G.ranked = q <= 9;
-    if (G.ranked)
-        for (uint32_t w = 0; w < nw; w++)
-            bits.push_back(words[w].y);
+    for (uint32_t w = 0; w < nw; w++)
+        bits.push_back(words[w].y);
     G.off_bits = append(ix->image, bits.data(), bits.size());
-    G.off_words = append(ix->image, words.data(), words.size());
     G.off_ents = append(ix->image, ents.data(), ents.size());
     G.off_strs = append(ix->image, strs.data(), strs.size());
     G.off_rows = append(ix->image, rows.data(), rows.size());

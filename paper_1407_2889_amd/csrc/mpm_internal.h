@@ -122,8 +122,8 @@ struct GramEnt {      // one (string, offset) of a gram
     uint32_t next;    // next entry of the same gram (all ones: none)
 };
 struct GramDev {
-    const uint32_t *bits;     // 4^q bits (and the second half of words), copied to LDS
-    const uint2 *words;       // per word of bits: (the word, grams before it)
+    const uint32_t *bits;     // 4^q bits, copied to LDS
+    const uint32_t *ranks;    // behind them: grams before each word of bits
     const GramEnt *ents;      // the first entry of gram number k at k, the others after them;
                               // a chain's offsets descend, longer strings first
     const uint2 *strs;        // per string: first 16-byte row, length
@@ -132,7 +132,7 @@ struct GramDev {
     const uint32_t *uids;
     uint32_t q, t_log, code_shift;
     uint32_t bit_bytes;       // bytes copied to LDS (multiple of 16)
-    uint32_t rank_off;        // where the second half of words starts there (0: not copied)
+    uint32_t rank_off;        // where the ranks start there (0: not copied)
     uint32_t main4;           // main byte of code k in byte k
     uint32_t m;               // shortest string
     uint32_t n_single;
@@ -332,7 +332,7 @@ struct mpm_index {
         uint32_t ok = 0, q = 0, t_log = 0, code_shift = 0, bit_bytes = 0, ranked = 0, main4 = 0;
         double cost = 0; // expected vector instructions per text byte (mpm_gram.cpp)
         double hit = 0;  // expected occurrences per text byte
-        uint64_t off_bits = 0, off_words = 0, off_ents = 0, off_strs = 0, off_rows = 0;
+        uint64_t off_bits = 0, off_ents = 0, off_strs = 0, off_rows = 0;
     } gram;
     // direct-address table (mpm_gram.cpp); ok = 0: the set has none
     struct Direct {

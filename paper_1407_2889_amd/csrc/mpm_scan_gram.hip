@@ -280,17 +280,17 @@ struct GramScan {
             pv[k] = __builtin_amdgcn_alignbit(B, A, sub);
         }
         uint2 w[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            w[k].x = *(lds_cptr<uint32_t>)lds_at<const uint8_t>(GBITS_OFF + ((code[k] & wmask) << 2));
         if (a.rank_off) {
 #pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const uint32_t y = (code[k] & wmask) << 2;
-                w[k].x = *(lds_cptr<uint32_t>)lds_at<const uint8_t>(GBITS_OFF + y);
-                w[k].y = *(lds_cptr<uint32_t>)lds_at<const uint8_t>(GBITS_OFF + a.rank_off + y);
-            }
+            for (int k = 0; k < K; ++k)
+                w[k].y = *(lds_cptr<uint32_t>)lds_at<const uint8_t>(GBITS_OFF + a.rank_off + ((code[k] & wmask) << 2));
         } else {
 #pragma unroll
             for (int k = 0; k < K; ++k)
-                w[k] = a.words[code[k] & wmask];
+                w[k].y = a.ranks[code[k] & wmask];
         }
 #pragma unroll
         for (int k = 0; k < K; ++k) {
@@ -754,7 +754,7 @@ GramDev gram_dev(const mpm_index *ix, uint32_t W)
     GramDev a;
     const uint8_t *img = ix->d_image;
     a.bits = (const uint32_t *)(img + G.off_bits);
-    a.words = (const uint2 *)(img + G.off_words);
+    a.ranks = a.bits + G.bit_bytes / 4;
     a.ents = (const GramEnt *)(img + G.off_ents);
     a.strs = (const uint2 *)(img + G.off_strs);
     a.rows = img + G.off_rows;
