@@ -303,6 +303,24 @@ void build_gram(mpm_index *ix)
     G.ranked = q <= 9;
     for (uint32_t w = 0; w < nw; w++)
         bits.push_back(words[w].y);
+    // With every position a sample (t = 1) the answers for two positions are
+    // read at once, two bits at the code of the q + 1 characters that both
+    // span (128 MiB, lengths 8-32: 66.2 -> 62.9 us; 64 MiB, d = 1000, m = 8 with
+    // counts 75.0 -> 72.5): 64 KiB at q = 8, which leaves the occurrence lists
+    // enough where occurrences are few.
+    if (G.ranked && bt == 0 && q <= 8 && G.hit <= 0.02) {
+        const uint32_t pw = 2 * q - 2;
+        std::vector<uint32_t> pairs(1u << pw, 0);
+        auto set = [&](uint32_t z, uint32_t k) { pairs[z & ((1u << pw) - 1u)] |= 1u << (2 * (z >> pw) + k); };
+        for (uint32_t u = 0; u < ix->du; u++)
+            for (uint32_t c = 0; c < 4; c++) {
+                const uint32_t g = (uint32_t)head[u] & gmask;
+                set(g | c << (2 * q), 0);
+                set(g << 2 | c, 1);
+            }
+        bits.insert(bits.end(), pairs.begin(), pairs.end());
+        G.pair_bytes = (uint32_t)(4 * pairs.size());
+    }
     G.off_bits = append(ix->image, bits.data(), bits.size());
     G.off_ents = append(ix->image, ents.data(), ents.size());
     G.off_strs = append(ix->image, strs.data(), strs.size());

@@ -1305,7 +1305,7 @@ static mpm_status plan_batch(const mpm_request *reqs, uint32_t count, bool sizin
                     slot[it.ix] = si;
                     index.push_back(it.ix);
                     if (g.kind == BK_GRAM) {
-                        g.gidx.push_back(gram_dev(it.ix));
+                        g.gidx.push_back(gram_dev(it.ix, GRAM_BATCH_W));
                     } else {
                         BatchIndex bi;
                         memset(&bi, 0, sizeof bi);

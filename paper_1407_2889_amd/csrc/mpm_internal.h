@@ -133,6 +133,7 @@ struct GramDev {
     uint32_t q, t_log, code_shift;
     uint32_t bit_bytes;       // bytes copied to LDS (multiple of 16)
     uint32_t rank_off;        // where the ranks start there (0: not copied)
+    uint32_t pair_off;        // where the two-position answers start there (0: not copied)
     uint32_t main4;           // main byte of code k in byte k
     uint32_t m;               // shortest string
     uint32_t n_single;
@@ -329,7 +330,7 @@ struct mpm_index {
 
     // q-gram filter (mpm_gram.cpp); ok = 0: the set has none
     struct Gram {
-        uint32_t ok = 0, q = 0, t_log = 0, code_shift = 0, bit_bytes = 0, ranked = 0, main4 = 0;
+        uint32_t ok = 0, q = 0, t_log = 0, code_shift = 0, bit_bytes = 0, ranked = 0, pair_bytes = 0, main4 = 0;
         double cost = 0; // expected vector instructions per text byte (mpm_gram.cpp)
         double hit = 0;  // expected occurrences per text byte
         uint64_t off_bits = 0, off_ents = 0, off_strs = 0, off_rows = 0;
@@ -426,7 +427,10 @@ void id_csr(const mpm_index *ix, const uint32_t **uoff, const uint32_t **uids);
 bool gram_takes(const mpm_index *ix, const mpm_variant *v, uint64_t n);
 bool gram_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, uint32_t lo, GramCfg *g);
 mpm_status gram_launch(const mpm_index *ix, const GramCfg &g, const ScanDev &sd, void *stream);
-GramDev gram_dev(const mpm_index *ix, uint32_t W = 1024);
+// W: the launch's workgroup size; batches have workgroups of 1024 threads, but
+// keep no two-position answers in LDS.
+static const uint32_t GRAM_BATCH_W = 512;
+GramDev gram_dev(const mpm_index *ix, uint32_t W);
 struct GramPieces {
     std::vector<GramPart> parts;
     std::vector<uint2> pieces;

@@ -12,7 +12,8 @@
 //      slower, 24 waves per CU instead of 16 as well.)
 //   2. One LDS bit per sample (every t-th position) tells whether the q-gram
 //      there occurs in a string at an offset below t: a shift, a mask, a
-//      ds_read, two shifts, one v_alignbit to collect the bit.
+//      ds_read, two shifts, one v_alignbit to collect the bit. (t = 1: two
+//      bits for two samples, where their table fits.)
 //   3. The block's candidates, in text order, are dealt to the lanes 128 at a
 //      time; each walks its gram's chain of (string, offset) entries and
 //      compares the codes of the string's first 16 characters.
@@ -28,11 +29,11 @@
 // (t = 8, q = 9, one candidate per 260 bytes) that is below what HBM asks for.
 //
 // Measured (EST-shaped text, walkers before, filter after, us): 256 MiB,
-// d = 1000, m = 16: AC 102 -> 62.6, WM 99 -> 62.5 (4.3 TB/s of text; while all
+// d = 1000, m = 16: AC 102 -> 62.5, WM 99 -> 62.5 (4.3 TB/s of text; while all
 // waves stream, 6.3 TB/s: the rest is the start and the wait for the slowest
 // wave); 128 MiB, d = 10k, m = 16, AC 366 -> 49; 64 MiB, d = 100k, m = 16, WM
-// 3554 -> 75; 64 MiB, d = 1000, m = 8 with counts, WM 421 -> 75; 128 MiB,
-// lengths 8-32, AC 134 -> 66; 32 MiB, lengths 8-32, WM 2110 -> 27.
+// 3554 -> 74; 64 MiB, d = 1000, m = 8 with counts, WM 421 -> 72; 128 MiB,
+// lengths 8-32, AC 134 -> 62; 32 MiB, lengths 8-32, WM 2110 -> 26.
 #include "mpm_gram.h"
 
 #include <cmath>
@@ -82,7 +83,7 @@ __device__ __forceinline__ void write_hits(mpm_match *out_, uint64_t cap, uint64
 // One wave's blocks [b0, b1). direct = false: count, keep the first `hcap`
 // occurrences in LDS; nh and nid (ids, summed over lanes) come back. direct =
 // true: write every pair from slot o on.
-template <int TL, bool Var>
+template <int TL, bool Var, bool Pair = false>
 struct GramScan {
     static constexpr uint32_t T = 1u << TL;
     static constexpr uint32_t NS = (16u * GN) >> TL;  // samples per lane and block
@@ -92,7 +93,7 @@ struct GramScan {
     IdMap im;
     uint32_t wv;    // LDS offset of this wave's buffers
     uint32_t hcap;
-    uint32_t amask, bsh, wmask;
+    uint32_t amask, bsh, wmask, pmask;
 
     __device__ __forceinline__ void bind(const GramDev &dev, const uint8_t *t, uint64_t n)
     {
@@ -109,6 +110,7 @@ struct GramScan {
         wmask = (1u << (2 * a.q - 5)) - 1u;
         amask = wmask << 2;
         bsh = 2 * a.q - 3;
+        pmask = ((1u << (2 * a.q - 2)) - 1u) << 2;
     }
 
     // Whether the len >= 4 bytes at view position s are string (row, len):
@@ -212,6 +214,13 @@ struct GramScan {
             for (uint32_t s = 0; s < NS; ++s) {
                 const uint32_t k = (s * T) >> 4, sub = 2 * ((s * T) & 15);
                 const uint32_t y = sub ? __builtin_amdgcn_alignbit(c[k + 1], c[k], sub - 2) : c[k] << 2;
+                if constexpr (Pair) {
+                    if (s & 1)
+                        continue;
+                    const uint32_t x = *(lds_cptr<uint32_t>)lds_at<const uint8_t>(GBITS_OFF + a.pair_off + (y & pmask));
+                    mk[s >> 5] = __builtin_amdgcn_alignbit(x >> (__builtin_amdgcn_ubfe(y, bsh + 3, 4) << 1), mk[s >> 5], 2);
+                    continue;
+                }
                 const uint32_t x = *(lds_cptr<uint32_t>)lds_at<const uint8_t>(GBITS_OFF + (y & amask));
                 mk[s >> 5] = __builtin_amdgcn_alignbit(x >> ((y >> bsh) & 31u), mk[s >> 5], 1);
             }
@@ -493,7 +502,7 @@ struct GramScan {
     }
 };
 
-template <int W, int TL, bool Var>
+template <int W, int TL, bool Var, bool Pair = false>
 __global__ __launch_bounds__(W) void gram_kernel(GramDev a, ScanDev sd, GramShare share, uint32_t hits,
                                                  uint32_t wave_bytes)
 {
@@ -515,7 +524,7 @@ __global__ __launch_bounds__(W) void gram_kernel(GramDev a, ScanDev sd, GramShar
     copy_to_lds<W>(GBITS_OFF, (const uint8_t *)a.bits, a.bit_bytes);
     load_groups(a.grp);
 
-    GramScan<TL, Var> sc;
+    GramScan<TL, Var, Pair> sc;
     sc.bind(a, sd.single.text, sd.single.n);
     sc.wv = GBITS_OFF + a.bit_bytes + wave * wave_bytes;
     sc.hcap = hits;
@@ -669,19 +678,23 @@ const void *pick(uint32_t tl, bool var)
     return nullptr;
 }
 
-const void *kernel_of(uint32_t W, uint32_t tl, bool var)
+const void *kernel_of(uint32_t W, uint32_t tl, bool var, bool pair)
 {
+    if (W == 1024 && tl == 0 && pair)
+        return var ? (const void *)gram_kernel<1024, 0, true, true> : (const void *)gram_kernel<1024, 0, false, true>;
     return W == 256 ? pick<256>(tl, var) : pick<1024>(tl, var);
 }
 
 }  // namespace
 
-// LDS bytes of the tables: the bits, and the grams before each word where
-// those pay for their copy: small workgroups share one of 32 KiB (q = 9)
-// between four waves only.
+// LDS bytes of the tables: the bits, the grams before each word where those
+// pay for their copy (small workgroups share one of 32 KiB, q = 9, between four
+// waves only), the two-position answers in the largest workgroups.
 static uint32_t lds_tables(const mpm_index::Gram &G, uint32_t W)
 {
-    return G.ranked && (W == 1024 || G.q <= 8) ? 2 * G.bit_bytes : G.bit_bytes;
+    if (!G.ranked || (W == 256 && G.q > 8))
+        return G.bit_bytes;
+    return 2 * G.bit_bytes + (W == 1024 ? G.pair_bytes : 0);
 }
 
 // Whether automatic placement runs an index through the filter.
@@ -724,7 +737,7 @@ bool gram_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, uint32_t
     g->lds_bytes = GBITS_OFF + lds_tables(G, W) + nw * g->wave_bytes;
     if (g->lds_bytes > (uint32_t)lim.max_lds)
         return false;
-    const void *k = kernel_of(W, G.t_log, ix->var != 0);
+    const void *k = kernel_of(W, G.t_log, ix->var != 0, G.pair_bytes != 0);
     if (g->lds_bytes > 65536)
         (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)g->lds_bytes);
     int nb = 0;
@@ -764,6 +777,7 @@ GramDev gram_dev(const mpm_index *ix, uint32_t W)
     a.code_shift = G.code_shift;
     a.bit_bytes = lds_tables(G, W);
     a.rank_off = a.bit_bytes > G.bit_bytes ? G.bit_bytes : 0;
+    a.pair_off = a.bit_bytes > 2 * G.bit_bytes ? 2 * G.bit_bytes : 0;
     a.main4 = G.main4;
     a.m = ix->m;
     a.n_single = ix->n_single;
@@ -781,7 +795,7 @@ mpm_status gram_launch(const mpm_index *ix, const GramCfg &g, const ScanDev &sd,
     GramShare share = g.share;
     uint32_t hits = g.hits, wave_bytes = g.wave_bytes;
     void *args[] = {&a, &s, &share, &hits, &wave_bytes};
-    const hipError_t e = hipLaunchKernel(kernel_of(g.W, ix->gram.t_log, ix->var != 0), dim3(g.grid), dim3(g.W),
+    const hipError_t e = hipLaunchKernel(kernel_of(g.W, ix->gram.t_log, ix->var != 0, ix->gram.pair_bytes != 0), dim3(g.grid), dim3(g.W),
                                          args, g.lds_bytes, (hipStream_t)stream);
     if (e != hipSuccess)
         return fail(MPM_EHIP, "scan launch: %s", hipGetErrorString(e));
@@ -793,7 +807,7 @@ mpm_status gram_launch(const mpm_index *ix, const GramCfg &g, const ScanDev &sd,
 bool gram_batch_takes(const mpm_index *ix, const mpm_variant *v, uint64_t n)
 {
     return ix->gram.ok && !ix->var && n < (1ull << 32) && gram_takes(ix, v, n) &&
-           GBITS_OFF + lds_tables(ix->gram, 1024) + 16 * (WV_HITS + 16 * 8) <= (uint32_t)limits().max_lds &&
+           GBITS_OFF + lds_tables(ix->gram, GRAM_BATCH_W) + 16 * (WV_HITS + 16 * 8) <= (uint32_t)limits().max_lds &&
            (uint64_t)(GBLOCK + 16) * std::max<uint64_t>(1, ix->max_dup) < (1ull << 32);
 }
 
@@ -821,7 +835,7 @@ void plan_gram_batch(const std::vector<const mpm_index *> &index, std::vector<Ba
     for (const mpm_index *ix : index) {
         const mpm_index::Gram &G = ix->gram;
         w.push_back(std::max(1.5, 0.85 * G.cost + 300.0 * G.hit));
-        const double fit = 0.6 * ((batch_wave_bytes(lds, lds_tables(G, 1024)) - WV_HITS) / 8) / (GBLOCK * G.hit);
+        const double fit = 0.6 * ((batch_wave_bytes(lds, lds_tables(G, GRAM_BATCH_W)) - WV_HITS) / 8) / (GBLOCK * G.hit);
         const uint64_t ids = ((1ull << 32) - 1) / std::max<uint64_t>(1, ix->max_dup);  // a part's count of ids: 32 bits
         most.push_back(std::max<uint64_t>(1, std::min<uint64_t>(fit > 4096 ? 4096 : (uint64_t)fit, (ids - 16) / GBLOCK)));
     }

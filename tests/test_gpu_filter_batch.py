@@ -159,3 +159,31 @@ def test_sync_scans_from_many_threads(mpm):
     for th in threads:
         th.join()
     assert not bad, bad
+
+
+@pytest.mark.parametrize("lens,d", [((8, 8), 1000), ((7, 7), 150), ((5, 5), 8), ((8, 32), 900), ((12, 12), 3000),
+                                    ((16, 16), 20_000), ((24, 24), 40_000)])
+def test_large_workgroups(mpm, lens, d):
+    """Texts of 16 MiB and a few bytes: workgroups of 1024 threads with the
+    answers for two positions, ranks in LDS, 4^10 bits, and waves with uneven
+    shares of the blocks; N runs and bytes that share a code."""
+    lo, hi = lens
+    t = synth.est_text((16 << 20) + 4 * 4096 + 77, seed=61)
+    t[5_000_000:5_000_400] = ord("N")
+    t[-300:] = ord("A")
+    P = synth.pattern_set(t, d, hi, d // 4, 62).patterns
+    P[0], P[1] = ord("A"), ord("N")
+    if lo != hi:
+        rng = np.random.default_rng(63)
+        P = [p[:n].tobytes() for p, n in zip(P, rng.integers(lo, hi + 1, d))]
+        ix = mpm.build_ac_var(P, upload=True)
+    else:
+        ix = mpm.build_wm(P, upload=True)
+    buf = torch.zeros(len(t) + 64, dtype=torch.uint8, device="cuda")
+    buf[5:5 + len(t)] = torch.from_numpy(t).cuda()
+    w = oracle.Win(P)
+    for n in (len(t), 16 << 20):
+        want = w.scan(t[:n])
+        say(f"[large] lengths {lens} d {d} n {n}: {len(want[0])} pairs")
+        got = mpm.pairs_numpy(mpm.scan(ix, buf[5:5 + n], capacity=len(want[0])))
+        assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
