@@ -408,6 +408,7 @@ struct GramCfg {
     uint32_t lds_bytes;
     uint32_t wave_bytes;   // LDS bytes of one wave's buffers
     uint32_t hits;         // occurrences a wave keeps in LDS
+    uint32_t tables_w;     // workgroup size that decides on the tables in LDS (gram_dev)
     uint64_t nblocks;      // blocks of the text
     uint64_t nchunks;
     bool direct;           // the direct-address scan

@@ -725,19 +725,27 @@ bool gram_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, uint32_t
     // the occurrence lists: all the LDS that is left to 16 waves (their
     // registers admit no second workgroup), 256 occurrences per wave of a
     // small workgroup
-    const uint32_t room = (uint32_t)lim.max_lds - GBITS_OFF - lds_tables(G, W);
-    if (room / nw < WV_HITS + 16 * 8)
+    auto hits_of = [&](uint32_t tables_w) {
+        const uint32_t room = ((uint32_t)lim.max_lds - GBITS_OFF - lds_tables(G, tables_w)) / nw;
+        return room < WV_HITS + 16 * 8 ? 0u : std::min<uint32_t>((room - WV_HITS) / 8, W == 1024 ? 1024 : 256) & ~1u;
+    };
+    // The two-position answers where the shorter lists still hold the expected
+    // occurrences of one round (1 GiB, d = 1000, m = 8, 16 rounds with them and
+    // 7 without: 1.97 against 2.02 TB/s; 64 MiB, one round: 72.5 against 75 us).
+    const uint64_t each = (nblocks + (uint64_t)lim.cus * nw - 1) / ((uint64_t)lim.cus * nw);
+    const bool pair = W == 1024 && G.pair_bytes && 0.6 * hits_of(W) >= (double)GBLOCK * G.hit * (double)each;
+    g->tables_w = W == 1024 && !pair ? GRAM_BATCH_W : W;
+    const uint32_t hits = hits_of(g->tables_w), tables = lds_tables(G, g->tables_w);
+    if (hits == 0)
         return false;
-    uint32_t hits = (room / nw - WV_HITS) / 8;
-    hits = std::min<uint32_t>(hits, W == 1024 ? 1024 : 256) & ~1u;
     g->nblocks = nblocks;
     g->W = W;
     g->hits = hits;
     g->wave_bytes = WV_HITS + 8 * hits;
-    g->lds_bytes = GBITS_OFF + lds_tables(G, W) + nw * g->wave_bytes;
+    g->lds_bytes = GBITS_OFF + tables + nw * g->wave_bytes;
     if (g->lds_bytes > (uint32_t)lim.max_lds)
         return false;
-    const void *k = kernel_of(W, G.t_log, ix->var != 0, G.pair_bytes != 0);
+    const void *k = kernel_of(W, G.t_log, ix->var != 0, pair);
     if (g->lds_bytes > 65536)
         (void)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)g->lds_bytes);
     int nb = 0;
@@ -789,13 +797,13 @@ mpm_status gram_launch(const mpm_index *ix, const GramCfg &g, const ScanDev &sd,
 {
     if (g.direct)
         return direct_launch(ix, g, sd, stream);
-    GramDev a = gram_dev(ix, g.W);
+    GramDev a = gram_dev(ix, g.tables_w);
     ScanDev s = sd;
     s.ntiles = g.nchunks;
     GramShare share = g.share;
     uint32_t hits = g.hits, wave_bytes = g.wave_bytes;
     void *args[] = {&a, &s, &share, &hits, &wave_bytes};
-    const hipError_t e = hipLaunchKernel(kernel_of(g.W, ix->gram.t_log, ix->var != 0, ix->gram.pair_bytes != 0), dim3(g.grid), dim3(g.W),
+    const hipError_t e = hipLaunchKernel(kernel_of(g.W, ix->gram.t_log, ix->var != 0, a.pair_off != 0), dim3(g.grid), dim3(g.W),
                                          args, g.lds_bytes, (hipStream_t)stream);
     if (e != hipSuccess)
         return fail(MPM_EHIP, "scan launch: %s", hipGetErrorString(e));
