@@ -644,9 +644,13 @@ public:
     void prepare()
     {
         std::lock_guard<std::mutex> g(mu_);
+        if (page_)
+            return;
         void *p = nullptr;
-        if (!page_ && hipHostMalloc(&p, SLOTS * sizeof(Slot), hipHostMallocPortable) == hipSuccess)
+        if (hipHostMalloc(&p, SLOTS * sizeof(Slot), hipHostMallocPortable) == hipSuccess)
             page_ = (Slot *)p;
+        else
+            (void)hipGetLastError();  // not the next launch's
     }
     Slot *take()
     {
