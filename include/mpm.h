@@ -374,11 +374,11 @@ typedef struct mpm_batch mpm_batch;
 /* Plan a batch: requests sharing (index, variant) are grouped into one
  * persistent launch whose workgroups take chunks of all the group's texts
  * from a shared ticket counter, each text keeping its own ordered output.
- * Requests that mpm_scan would run through the q-gram filter (texts of 64
- * bytes or more) form one launch of their own, whatever their indexes; its
- * waves take pieces of equal expected time, of one or more texts. (With
- * MPM_VARIANT_ILP2, which a batch otherwise ignores, a request stays with the
- * walkers.)
+ * Requests under MPM_PLACE_AUTO (no flags but MPM_VARIANT_DENSE) whose set has
+ * a q-gram filter and whose text has 64 bytes or more form one launch of their
+ * own, whatever their indexes; its waves take pieces of equal expected time,
+ * of one or more texts. (With MPM_VARIANT_ILP2, which a batch otherwise
+ * ignores, a request stays with the walkers.)
  * The plan copies the request array. Host-only.
  * Errors: EINVAL, ETOOBIG, ENOMEM. */
 mpm_status mpm_batch_plan(const mpm_request *reqs, uint32_t count, mpm_batch **out);
