@@ -307,9 +307,11 @@ mpm_status mpm_scan_sync(const mpm_index *idx, const uint8_t *d_text, uint64_t n
 /* Scan a text that stays in host memory (Section 5: the texts exceeded device
  * memory and the kernels read them from host memory). The text is cut into
  * chunks of `chunk` starting positions; each chunk and the m - 1 bytes after
- * it are copied into one half of d_stage on a copy stream the call creates
- * (default priority) while the previous chunk is scanned on `stream`. Waits
- * for completion; the result is that of mpm_scan_sync on the whole text.
+ * it are copied into one half of d_stage on a copy stream of the call's own
+ * (default priority; kept in a process-wide pool between calls), after all
+ * work queued on `stream` before the call, while the previous chunk is scanned
+ * on `stream`. Waits for completion; the result is that of mpm_scan_sync on
+ * the whole text.
  *   h_text:      host, n bytes. Pinned memory (hipHostMalloc) lets the copies
  *                overlap the scans; pageable memory works, serialized.
  *   d_stage:     device staging buffer of stage_bytes >= 2 * (c + m - 1)
