@@ -7,12 +7,6 @@
 namespace mpm {
 namespace {
 
-// Set in the epoch of these scans' status words. Their chunks differ from the
-// walkers', so on a shared workspace a status word may hold what a walker
-// staged there, a (position, string) pair: its top bit, and so this bit of
-// the epoch field, is clear.
-constexpr uint32_t GRAM_EPOCH = 1u << 25;
-
 typedef v4u v4u_any __attribute__((aligned(1)));
 typedef uint64_t u64_any __attribute__((aligned(1)));
 typedef uint32_t u32_any __attribute__((aligned(1)));
@@ -181,7 +175,7 @@ __device__ __forceinline__ uint64_t wave_offset(uint32_t cnt, uint64_t *s_scan, 
     const uint64_t agg = uniform64(c), before = uniform64(b4);
     uint64_t part = 0;
     if (ntiles <= WIDE_CHUNKS) {
-        const uint64_t tag = epoch & ST_EPOCH_MASK;
+        const uint64_t tag = status_tag(epoch);
         if (threadIdx.x == 0)
             st_status(&status[g], make_status(epoch, 1, agg));
         if (agg == 0 && g + 1 != ntiles)  // nothing to place

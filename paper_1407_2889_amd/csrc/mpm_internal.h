@@ -272,10 +272,14 @@ struct GramBatchDev {
 // stage at most this many.
 static const uint32_t BATCH_STAGE_CAP = 16;
 
-// Look-back status word: [63:38] epoch, [37:36] flag, [35:0] value.
+// Look-back status word: [63:38] tag, [37:36] flag, [35:0] value. The tag is
+// the launch epoch with its top bit set. On a workspace that serves texts of
+// different lengths, or walkers and filter scans, a status word may hold what
+// an earlier scan staged there, a (position, string) pair: string numbers stay
+// below 2^31, so its top bit is clear and it is no word of any epoch.
 static const uint64_t ST_VAL_BITS = 36;
 static const uint64_t ST_VAL_MASK = (1ull << ST_VAL_BITS) - 1;
-static const uint32_t ST_EPOCH_MASK = (1u << 26) - 1;
+static const uint32_t ST_TAG_BIT = 1u << 25;
 
 }  // namespace mpm
 

@@ -414,7 +414,7 @@ __global__ __launch_bounds__(W) void direct_kernel(DirectDev a, ScanDev sd, Gram
             break;
         const uint64_t b0 = share.first(g * NW + wave), b1 = share.first(g * NW + wave + 1);
         const uint32_t n = sc.count(hidden(b0), b1);
-        const uint64_t o = wave_offset<W>(n, s_scan, sd.status, g, sd.ntiles, sd.single.total, s_epoch | GRAM_EPOCH,
+        const uint64_t o = wave_offset<W>(n, s_scan, sd.status, g, sd.ntiles, sd.single.total, s_epoch,
                                           &hdr[WS_ERR]);
         if (n && o < sd.single.cap)
             sc.write(hidden(b0), b1, sd.single.out, sd.single.cap, o);

@@ -538,7 +538,7 @@ __global__ __launch_bounds__(W) void gram_kernel(GramDev a, ScanDev sd, GramShar
             break;
         const uint64_t b0 = share.first(g * NW + wave), b1 = share.first(g * NW + wave + 1);
         sc.part(b0, b1, sd.single.out, cap, [&](uint32_t nid) {
-            return wave_offset<W>(nid, s_scan, sd.status, g, ntiles, sd.single.total, s_epoch | GRAM_EPOCH,
+            return wave_offset<W>(nid, s_scan, sd.status, g, ntiles, sd.single.total, s_epoch,
                                   &hdr[WS_ERR]);
         });
         if (gridDim.x >= ntiles)  // one chunk per workgroup

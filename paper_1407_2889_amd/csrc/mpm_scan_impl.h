@@ -139,9 +139,14 @@ __device__ __forceinline__ void st_status(uint64_t *p, uint64_t v)
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+__device__ __forceinline__ uint32_t status_tag(uint32_t epoch)
+{
+    return (epoch & (ST_TAG_BIT - 1u)) | ST_TAG_BIT;
+}
+
 __device__ __forceinline__ uint64_t make_status(uint32_t epoch, uint32_t flag, uint64_t val)
 {
-    return ((uint64_t)(epoch & ST_EPOCH_MASK) << 38) | ((uint64_t)flag << ST_VAL_BITS) |
+    return ((uint64_t)status_tag(epoch) << 38) | ((uint64_t)flag << ST_VAL_BITS) |
            (val & ST_VAL_MASK);
 }
 
@@ -161,7 +166,7 @@ __device__ __forceinline__ uint64_t look_back(uint64_t *status, uint64_t g, uint
     }
     if (lane == 0)
         st_status(&status[g], make_status(epoch, 1, agg));
-    const uint64_t tag = epoch & ST_EPOCH_MASK;
+    const uint64_t tag = status_tag(epoch);
     uint64_t excl = 0;
     int64_t top = (int64_t)g - 1;  // status index probed by lane 0
     uint32_t spins = 0;
