@@ -198,6 +198,7 @@ void build_gram(mpm_index *ix)
     const std::vector<uint64_t> head = head_codes(ix, S, sh);
     std::vector<uint8_t> count;
     double best = 1e300, chosen = 1e300;
+    Rate rate = {0, 0, 0};
     uint32_t bq = 0, bt = 0;
     for (size_t k = 0; k < all.size() && k < 4 && (all[k].cost < 0.9 * chosen || best > 25.0); k++) {
         if (all[k].plain >= 25.0)
@@ -210,6 +211,7 @@ void build_gram(mpm_index *ix)
         const double c = cost_of(all[k].q, tk, r.cand * spread_of(tk, ix->du), r.steps);
         if (c < chosen) {
             chosen = c;
+            rate = r;
             bq = all[k].q;
             bt = all[k].tl;
         }
@@ -325,6 +327,26 @@ void build_gram(mpm_index *ix)
     G.off_ents = append(ix->image, ents.data(), ents.size());
     G.off_strs = append(ix->image, strs.data(), strs.size());
     G.off_rows = append(ix->image, rows.data(), rows.size());
+    if (ix->algo == MPM_ALGO_AC && std::max(m, ix->m_max) < (1u << 20)) {  // (32-bit places in a lane's walk)
+        GramWalk w;
+        memset(&w, 0, sizeof w);
+        w.self = (ix->image.size() + 255) / 256 * 256;
+        w.dfa = ix->off_a;
+        w.cls = ix->off_b;
+        w.term = ix->var ? ix->off_e : 0;
+        w.rowb = (ix->n_classes + 1) * ix->state_bytes;
+        w.first_term = (uint32_t)(ix->var ? ix->first_term : ix->n_states - ix->du);
+        w.wide = ix->state_bytes == 4;
+        w.past = (ix->var ? ix->m_max : m) - 1;
+        G.off_walk = append(ix->image, &w, 1);
+        // Twice the candidates that a block should have, and one batch more:
+        // up to that a block takes about what the choice of q and t counted
+        // on. (At least an eighth of the samples instead: 256 MiB of records
+        // with poly-A tails, m = 8, 1750 -> 1480 us, but lengths 8-32 with 50
+        // strings of one head of nine A 880 -> 1220.) Wu-Manber indexes have
+        // no automaton, and their own walk takes as long on such texts.
+        G.crowd = (uint32_t)(64 + 2 * 4096 * rate.cand);
+    }
     ix->image.resize((ix->image.size() + 255) / 256 * 256, 0);
     G.ok = 1;
 }

@@ -121,6 +121,13 @@ struct GramEnt {      // one (string, offset) of a gram
                       // the main byte of its code, so that key tells the bytes
     uint32_t next;    // next entry of the same gram (all ones: none)
 };
+struct GramWalk {     // an Aho-Corasick index's automaton, for crowded blocks; kept in the image
+    uint64_t self, dfa, cls, term;  // byte offsets in the image: this struct, the table, the columns, term_u
+    uint32_t rowb;        // bytes of a table row
+    uint32_t first_term;
+    uint32_t wide;        // 32-bit table entries
+    uint32_t past;        // bytes a walk reads past its starting positions
+};
 struct GramDev {
     const uint32_t *bits;     // 4^q bits, copied to LDS
     const uint32_t *ranks;    // behind them: grams before each word of bits
@@ -137,6 +144,8 @@ struct GramDev {
     uint32_t main4;           // main byte of code k in byte k
     uint32_t m;               // shortest string
     uint32_t n_single;
+    uint32_t crowd;           // candidates of a block past which it is walked (all ones: no automaton)
+    const GramWalk *walk;
     IdGroups grp;
 };
 
@@ -338,6 +347,8 @@ struct mpm_index {
         double cost = 0; // expected vector instructions per text byte (mpm_gram.cpp)
         double hit = 0;  // expected occurrences per text byte
         uint64_t off_bits = 0, off_ents = 0, off_strs = 0, off_rows = 0;
+        uint32_t crowd = 0xffffffffu;
+        uint64_t off_walk = 0;
     } gram;
     // direct-address table (mpm_gram.cpp); ok = 0: the set has none
     struct Direct {

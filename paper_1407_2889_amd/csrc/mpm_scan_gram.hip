@@ -80,6 +80,20 @@ __device__ __forceinline__ void write_hits(mpm_match *out_, uint64_t cap, uint64
     o += total;
 }
 
+// A descriptor at a uniform address that no launch writes, by scalar loads.
+template <class T>
+__device__ __forceinline__ T uniform_load(const T *p)
+{
+    typedef const __attribute__((address_space(4))) uint32_t *words;
+    uint32_t w[sizeof(T) / 4];
+#pragma unroll
+    for (uint32_t k = 0; k < sizeof(T) / 4; ++k)
+        w[k] = ((words)(uintptr_t)p)[k];
+    T t;
+    __builtin_memcpy(&t, w, sizeof t);
+    return t;
+}
+
 // One wave's blocks [b0, b1). direct = false: count, keep the first `hcap`
 // occurrences in LDS; nh and nid (ids, summed over lanes) come back. direct =
 // true: write every pair from slot o on.
@@ -250,6 +264,20 @@ struct GramScan {
             }
             const uint32_t incl = wave_incl_sum(cnt);
             const uint32_t tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+            if (__builtin_expect(tot > 64, 0) && tot > a.crowd) {  // (crowd >= 64)
+                // the lane's first and last candidate
+                uint32_t f = 0, l = 0;
+#pragma unroll
+                for (uint32_t h = 0; h < NM; ++h) {
+                    f = mk[NM - 1 - h] ? 32 * (NM - 1 - h) + (uint32_t)__builtin_ctz(mk[NM - 1 - h]) : f;
+                    l = mk[h] ? 32 * h + 31 - (uint32_t)__builtin_clz(mk[h]) : l;
+                }
+                crowded(direct, hidden(b) * GBLOCK, cnt != 0, f, l, nh, nid, out, cap, o);
+                // again, as they are not kept in registers over the walk
+                // (of the last blocks: any block's)
+                text.load(hidden(min(b + 2, b1 - 1)) * GBLOCK, lane, r);
+                continue;
+            }
             uint32_t rk = incl - cnt;  // place of the lane's next candidate
 #pragma unroll 1
             for (uint32_t win = 0; win < tot; win += 128) {
@@ -264,6 +292,150 @@ struct GramScan {
                 else
                     candidates<1>(direct, b * GBLOCK, tot - win, nh, nid, last, out, cap, o);
             }
+        }
+    }
+
+    // The starting positions that a block's samples stand for, with the
+    // index's automaton: each lane its own, from its first candidate to its
+    // last, counted, then walked again for their pairs. For blocks with more
+    // candidates than the set's text should have (a.crowd, mpm_gram.cpp): runs
+    // of one character (poly-A tails; N, which shares G's code) and short
+    // repeats whose grams are in the set make every sample a candidate, with a
+    // chain of entries and strings to compare at each, where a walk takes a
+    // table row per byte. It is bound by the rows' round trips to L1 and L2.
+    // Measured, d = 1000, us by the candidates, by the walk here, and by the
+    // walkers of explicit placements: a tenth of the text in runs of N, G^m in
+    // the set, m = 16: 32 MiB 324, 57, 81, 256 MiB 2077, 141, 101; m = 24: 489,
+    // 87, 110, and 3215, 183, 128; all A, A^8 in the set, 32 MiB: 762, 280, 212;
+    // lengths 8-32 with 50 strings of one head of nine A, 256 MiB of A: 9608,
+    // 236, 118, of records with poly-A tails: 1504, 939, 145 (958 in the
+    // default launch shape): there the table outgrows the L1. (Four bytes per
+    // turn are 7 % faster here and cost the batch 1 % more for their code.)
+    // Texts without such blocks: 256 MiB, m = 16, 62.1 -> 61.7; lengths 8-32,
+    // 128 MiB, 62.2 -> 62.1; the batch of 256 texts 109 -> 111.
+    __device__ __forceinline__ void crowded(bool direct, uint64_t base, bool any, uint32_t fs, uint32_t ls,
+                                            uint32_t &nh, uint32_t &nid, mpm_match *out, uint64_t cap,
+                                            uint64_t &o) const
+    {
+        const uint32_t lane = threadIdx.x & 63u;
+        const GramWalk w = uniform_load(a.walk);
+        glb_cptr<uint8_t> img = (glb_cptr<uint8_t>)a.walk - w.self;
+        glb_cptr<uint16_t> cls = (glb_cptr<uint16_t>)(img + w.cls);
+        const int64_t first = (int64_t)base - (int64_t)(T - 1);  // the wave's first start
+        // Positions from here on are relative to it. The lane's starts [s0, s1],
+        // those of its first to its last candidate.
+        const int32_t s0 = (int32_t)(64 * lane + T * fs), s1 = (int32_t)(64 * lane + T * ls + T - 1);
+        glb_cptr<uint8_t> tx = text.p + first;
+        const int32_t lo = (int32_t)max((int64_t)text.lo - first, -((int64_t)1 << 30));
+        const int32_t end = (int32_t)min((int64_t)text.hi - first, (int64_t)1 << 30);
+        const bool whole = lo <= 0 && (int32_t)(GBLOCK + w.past + 16) <= end;
+        // 16 bytes at v; ok: which of them lie in the text (the others restart the walk)
+        auto piece = [&](int32_t v, uint32_t &ok) {
+            if (whole) {
+                ok = 0xffffu;
+                return *(const GLB_AS v4u_any *)(tx + v);
+            }
+            v4u c = {0, 0, 0, 0};
+            ok = 0;
+#pragma unroll 1
+            for (uint32_t k = 0; k < 16; ++k) {
+                const int32_t x = v + (int32_t)k;
+                c = v4u{__builtin_amdgcn_alignbit(c.y, c.x, 8), __builtin_amdgcn_alignbit(c.z, c.y, 8),
+                        __builtin_amdgcn_alignbit(c.w, c.z, 8), c.w >> 8};
+                if (x >= lo && x < end) {
+                    c.w |= (uint32_t)tx[x] << 24;
+                    ok |= 1u << k;
+                }
+            }
+            return c;
+        };
+        uint32_t hits = 0, ids = 0, slot = 0;
+        uint64_t ob = 0;
+#pragma unroll 1
+        for (uint32_t pass = 0; pass < 2; ++pass) {
+            uint32_t np = any ? (uint32_t)(s1 - s0 + w.past + 16) >> 4 : 0u;  // pieces, of the lane's own
+            const int32_t step = Var ? -16 : 16;
+            int32_t v = Var ? s0 + 16 * (int32_t)np - 16 : s0;
+            uint32_t s = 0, okn = 0, entry = 0xffffffffu;
+            v4u cn = {0, 0, 0, 0}, was = cn;
+            if (np)
+                cn = piece(v, okn);
+#pragma unroll 1
+            for (uint32_t j = 0; __ballot(j < np) != 0; ++j, v += step) {
+                if (j >= np)
+                    continue;
+                v4u c = cn;
+                uint32_t ok = okn;
+                if (j + 1 < np)
+                    cn = piece(v + step, okn);
+                // The piece of before again, from the state that it left as it
+                // found it and without a string: it does the same (runs and
+                // repeats of 2, 4, 8 or 16 characters).
+                const bool same = s == entry && ok == 0xffffu && ((c.x ^ was.x) | (c.y ^ was.y) | (c.z ^ was.z) | (c.w ^ was.w)) == 0;
+                if (__ballot(!same) == 0)
+                    continue;
+                entry = s;
+                was = c;
+                // one byte per turn, the next one's column requested beside its row
+                uint32_t col = cls[Var ? c.w >> 24 : c.x & 0xffu];
+#pragma unroll 1
+                for (uint32_t k = 0; k < 16; ++k) {
+                    c = Var ? v4u{c.x << 8, __builtin_amdgcn_alignbit(c.y, c.x, 24), __builtin_amdgcn_alignbit(c.z, c.y, 24),
+                                  __builtin_amdgcn_alignbit(c.w, c.z, 24)}
+                            : v4u{__builtin_amdgcn_alignbit(c.y, c.x, 8), __builtin_amdgcn_alignbit(c.z, c.y, 8),
+                                  __builtin_amdgcn_alignbit(c.w, c.z, 8), c.w >> 8};
+                    const uint32_t off = s * w.rowb + col;
+                    col = cls[Var ? c.w >> 24 : c.x & 0xffu];
+                    s = w.wide ? *(glb_cptr<uint32_t>)(img + w.dfa + off) : *(glb_cptr<uint16_t>)(img + w.dfa + off);
+                    const uint32_t i = Var ? 15 - k : k;
+                    if (!(ok >> i & 1u))
+                        s = 0;
+                    if (s < w.first_term)
+                        continue;
+                    entry = 0xffffffffu;
+                    const int32_t at = v + (int32_t)i - (Var ? 0 : (int32_t)w.past);
+                    if (at > s1)
+                        continue;
+                    uint32_t u = s - w.first_term;
+                    if (Var)
+                        u = ((glb_cptr<uint32_t>)(img + w.term))[u];
+                    uint32_t ib, ie;
+                    im.span(u, ib, ie);
+                    if (pass == 0) {
+                        ++hits;
+                        ids += ie - ib;
+                        continue;
+                    }
+                    const uint32_t pos = (uint32_t)(first - (int64_t)text.lo) + (uint32_t)at;
+                    if (Var)
+                        ob -= ie - ib, --slot;
+                    if (direct) {
+                        for (uint32_t t = ib; t < ie; ++t)
+                            if (ob + (t - ib) < cap)
+                                ((GLB_AS v2u *)out)[ob + (t - ib)] = v2u{pos, im.id(t)};
+                    } else {
+                        lds_at<v2u>(wv + WV_HITS)[slot] = v2u{pos, u};
+                    }
+                    if (!Var)
+                        ob += ie - ib, ++slot;
+                }
+                if (!Var && s == 0 && v + 16 > s1)  // nothing begun up to the last start
+                    np = j + 1;
+            }
+            if (pass)
+                break;
+            // places of the lane's occurrences and pairs (Var: those after its last)
+            const uint32_t hi = wave_incl_sum(hits), ii = wave_incl_sum(ids);
+            const uint32_t th = (uint32_t)__builtin_amdgcn_readlane((int)hi, 63);
+            const uint32_t ti = (uint32_t)__builtin_amdgcn_readlane((int)ii, 63);
+            slot = nh + (Var ? hi : hi - hits);
+            ob = o + (Var ? ii : ii - ids);
+            const uint64_t o0 = o;
+            nid += ids;
+            nh += th;
+            o += ti;
+            if (th == 0 || (direct ? o0 >= cap : nh > hcap))
+                break;
         }
     }
 
@@ -554,20 +726,6 @@ __global__ __launch_bounds__(W) void gram_kernel(GramDev a, ScanDev sd, GramShar
     finish_launch(hdr, s_epoch);
 }
 
-// A descriptor at a uniform address that no launch writes, by scalar loads.
-template <class T>
-__device__ __forceinline__ T uniform_load(const T *p)
-{
-    typedef const __attribute__((address_space(4))) uint32_t *words;
-    uint32_t w[sizeof(T) / 4];
-#pragma unroll
-    for (uint32_t k = 0; k < sizeof(T) / 4; ++k)
-        w[k] = ((words)(uintptr_t)p)[k];
-    T t;
-    __builtin_memcpy(&t, w, sizeof t);
-    return t;
-}
-
 // Batched texts. A wave takes a piece: parts (runs of blocks) of one or more
 // texts of an index, of about equal expected time in every piece
 // (plan_gram_batch). Sixteen pieces of an index are a ticket; the workgroup
@@ -789,6 +947,8 @@ GramDev gram_dev(const mpm_index *ix, uint32_t W)
     a.main4 = G.main4;
     a.m = ix->m;
     a.n_single = ix->n_single;
+    a.crowd = G.crowd;
+    a.walk = (const GramWalk *)(img + G.off_walk);
     a.grp = id_groups(ix);
     return a;
 }
