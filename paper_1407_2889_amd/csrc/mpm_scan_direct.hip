@@ -21,6 +21,10 @@
 // bytes of no pattern, make a window "odd". Odd windows take nothing from the
 // table; the few strings that hold such bytes themselves have a bit table
 // over the same codes, and windows that pass it are compared byte by byte.
+// In a run of N that is every window: each lane then looks up its own, two in
+// flight (32 MiB, d = 10k, m = 8, N^8 in the set, a tenth in runs of N: 1894 ->
+// 319 us, the dense-output walkers 213; a list of 64 windows at a time, as for
+// the few of other texts, costs its round trips 64 times per block and pass).
 //
 // Measured against the dense-output walkers (EST-shaped text, m = 8, us, before
 // and after): 64 MiB, d = 10k 398 -> 189, d = 100k (92 M pairs) 856 -> 368;
@@ -74,24 +78,51 @@ struct DirectScan {
     uint32_t split;  // log2 of the waves that share a block's positions
     uint32_t amask;  // byte offsets of the table's words
 
-    // Ids [s, s + n) of the odd string with these codes at view position v
-    // (n = 0: none).
-    __device__ __forceinline__ void odd_string(uint64_t v, uint32_t code, uint32_t &s, uint32_t &n) const
+    // Ids [s, s + n) of the odd strings with these codes at view positions v,
+    // where `on` (n = 0: none); the others stay as they are. The K lookups'
+    // loads are in flight together.
+    template <int K>
+    __device__ __forceinline__ void odd_strings(const uint64_t (&v)[K], const uint32_t (&code)[K], const bool (&on)[K],
+                                                uint32_t (&s)[K], uint32_t (&n)[K]) const
     {
-        const uint2 w = a.odd_words[code >> 5];
-        const uint64_t at = T.inside(v);
-        const uint64_t t = *(const GLB_AS u64_any *)(T.p + at), t2 = *(const GLB_AS u64_any *)(T.p + at + 8);
-        const uint32_t d = 8 * (uint32_t)(v - at);  // the window lies inside the piece
         const uint64_t keep = a.m == 8 ? ~0ull : (1ull << (8 * a.m)) - 1ull;
-        const uint64_t bytes = (d == 0 ? t : d < 64 ? t >> d | t2 << (64 - d) : t2 >> (d - 64)) & keep;
-        for (uint32_t i = w.y + __popc(w.x & ((1u << (code & 31u)) - 1u)); i != 0xffffffffu;) {
-            const OddEnt e = a.odd_ents[i];
-            if (e.bytes == bytes) {
-                s = e.first;
-                n = e.count;
-                return;
-            }
-            i = e.next;
+        uint2 w[K];
+        uint64_t t[K], t2[K];
+        uint32_t i[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const uint64_t at = T.inside(on[k] ? v[k] : T.lo);
+            w[k] = a.odd_words[on[k] ? code[k] >> 5 : 0u];
+            t[k] = *(const GLB_AS u64_any *)(T.p + at);
+            t2[k] = *(const GLB_AS u64_any *)(T.p + at + 8);
+        }
+        bool more = false;
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const uint32_t d = 8 * (uint32_t)(v[k] - T.inside(v[k]));  // the window lies inside the piece
+            t[k] = (d == 0 ? t[k] : d < 64 ? t[k] >> d | t2[k] << (64 - d) : t2[k] >> ((d - 64) & 63)) & keep;
+            i[k] = on[k] ? w[k].y + __popc(w[k].x & ((1u << (code[k] & 31u)) - 1u)) : 0xffffffffu;
+            if (on[k])
+                n[k] = 0;
+            more |= on[k];
+        }
+        while (more) {
+            OddEnt e[K];
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                e[k] = a.odd_ents[i[k] != 0xffffffffu ? i[k] : 0u];
+            more = false;
+#pragma unroll
+            for (int k = 0; k < K; ++k)
+                if (i[k] != 0xffffffffu) {
+                    const bool eq = e[k].bytes == t[k];
+                    if (eq) {
+                        s[k] = e[k].first;
+                        n[k] = e[k].count;
+                    }
+                    i[k] = eq ? 0xffffffffu : e[k].next;
+                    more |= i[k] != 0xffffffffu;
+                }
         }
     }
     __device__ __forceinline__ bool odd_bit(uint32_t code) const
@@ -99,40 +130,52 @@ struct DirectScan {
         return lds_at<const uint32_t>(obits)[code >> 5] >> (code & 31u) & 1u;
     }
 
+    __device__ __forceinline__ uint32_t code_at(uint32_t p) const
+    {
+        LDS_AS uint32_t *cw = lds_at<uint32_t>(wv);
+        const uint32_t wi = 4 + (p >> 4);
+        return __builtin_amdgcn_alignbit(cw[wi + 1], cw[wi], 2 * (p & 15u)) & cmask();
+    }
+
     // Of a block's odd windows (one bit per position of the lane) those with an
-    // odd string's codes, for the whole wave: few, so that they are looked up
-    // together, 64 at a time, found(position, s, n) per lane. Returns the bits,
-    // tot their number.
-    template <class F>
-    __device__ __forceinline__ uint64_t odd_windows(uint64_t vb, uint64_t odd, uint32_t &tot, F found) const
+    // odd string's codes: their bits, tot their number in the wave.
+    __device__ __forceinline__ uint64_t odd_hits(uint64_t odd, uint32_t &incl, uint32_t &tot) const
     {
         const uint32_t lane = threadIdx.x & 63u;
-        LDS_AS uint32_t *cw = lds_at<uint32_t>(wv);
-        LDS_AS uint32_t *list = lds_at<uint32_t>(wv + DW_LIST);
         uint64_t hit = 0;
         for (uint64_t q = odd; q; q &= q - 1) {
-            const uint32_t j = (uint32_t)__builtin_ctzll(q), wi = 4 + 4 * lane + (j >> 4);
-            if (odd_bit(__builtin_amdgcn_alignbit(cw[wi + 1], cw[wi], 2 * (j & 15u)) & cmask()))
+            const uint32_t j = (uint32_t)__builtin_ctzll(q);
+            if (odd_bit(code_at(64 * lane + j)))
                 hit |= 1ull << j;
         }
-        const uint32_t mine = (uint32_t)__popcll(hit), incl = wave_incl_sum(mine);
+        incl = wave_incl_sum((uint32_t)__popcll(hit));
         tot = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-#pragma unroll 1
-        for (uint32_t win = 0; win < tot; win += 64) {
-            wave_sync();
-            uint32_t at = incl - mine - win;  // below 64: this window's place
-            for (uint64_t q = hit; q; q &= q - 1, ++at)
-                if (at < 64)
-                    list[at] = 64 * lane + (uint32_t)__builtin_ctzll(q);
-            wave_sync();
-            if (lane < tot - win) {
-                const uint32_t p = list[lane], wi = 4 + (p >> 4);
-                uint32_t s = 0, n = 0;
-                odd_string(vb + p, __builtin_amdgcn_alignbit(cw[wi + 1], cw[wi], 2 * (p & 15u)) & cmask(), s, n);
-                found(p, s, n);
-            }
-        }
         return hit;
+    }
+
+    // At most 64 of them, as there usually are: one per lane, positions to the
+    // list; s, n: this lane's string.
+    __device__ __forceinline__ void odd_few(uint64_t vb, uint64_t hit, uint32_t incl, uint32_t tot, uint32_t &s,
+                                            uint32_t &n) const
+    {
+        const uint32_t lane = threadIdx.x & 63u;
+        LDS_AS uint32_t *list = lds_at<uint32_t>(wv + DW_LIST);
+        uint32_t at = incl - (uint32_t)__popcll(hit);
+        wave_sync();
+        for (uint64_t q = hit; q; q &= q - 1, ++at)
+            list[at] = 64 * lane + (uint32_t)__builtin_ctzll(q);
+        wave_sync();
+        s = n = 0;
+        if (lane < tot) {
+            const uint32_t p = list[lane];
+            const uint64_t v[1] = {vb + p};
+            const uint32_t code[1] = {code_at(p)};
+            const bool on[1] = {true};
+            uint32_t s1[1] = {0}, n1[1] = {0};
+            odd_strings<1>(v, code, on, s1, n1);
+            s = s1[0];
+            n = n1[0];
+        }
     }
 
     // Units [u0, u1) of a wave: unit u is part u mod 2^split of block
@@ -226,8 +269,31 @@ struct DirectScan {
             }
             if (a.odd_bytes) {
                 wave_sync();
-                uint32_t tot;
-                (void)odd_windows(vb, odd, tot, [&](uint32_t, uint32_t, uint32_t n) { sum += n; });
+                uint32_t incl, tot;
+                uint64_t hit = odd_hits(odd, incl, tot);
+                if (tot > 64) {
+                    // a run of odd characters: each lane its own, two at a time
+                    while (hit) {
+                        uint64_t v[2];
+                        uint32_t code[2], s[2], n[2];
+                        bool on[2];
+#pragma unroll
+                        for (int k = 0; k < 2; ++k) {
+                            const uint32_t p = 64 * lane + (hit ? (uint32_t)__builtin_ctzll(hit) : 0u);
+                            on[k] = hit != 0;
+                            v[k] = vb + p;
+                            code[k] = code_at(p);
+                            s[k] = n[k] = 0;
+                            hit &= hit - 1;
+                        }
+                        odd_strings<2>(v, code, on, s, n);
+                        sum += n[0] + n[1];
+                    }
+                } else if (tot) {
+                    uint32_t s, n;
+                    odd_few(vb, hit, incl, tot, s, n);
+                    sum += n;
+                }
             }
         }
         return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_sum(sum), 63);
@@ -278,10 +344,14 @@ struct DirectScan {
             uint32_t nodd = 0;
             if (a.odd_bytes) {
                 wave_sync();
-                odd = odd_windows(vb, in_part(b, lane) ? odd : 0, nodd, [&](uint32_t, uint32_t s, uint32_t n) {
+                uint32_t incl;
+                odd = odd_hits(in_part(b, lane) ? odd : 0, incl, nodd);
+                if (nodd && nodd <= 64) {
+                    uint32_t s, n;
+                    odd_few(vb, odd, incl, nodd, s, n);
                     list[64 + lane] = s;
                     list[128 + lane] = n;
-                });
+                }
                 lds_at<uint64_t>(wv + DW_ODD)[lane] = odd;
             }
             lds_at<uint64_t>(wv + DW_KEEP)[lane] = keep;
@@ -318,9 +388,16 @@ struct DirectScan {
                             }
                         } else {
 #pragma unroll
-                            for (uint32_t k = 0; k < 4; ++k)
-                                if (od >> k & 1u)
-                                    odd_string(vb + 256 * i + 4 * lane + k, (x >> (2 * k)) & cmask(), s[k], n[k]);
+                            for (uint32_t k = 0; k < 4; k += 2) {
+                                const uint64_t v = vb + 256 * i + 4 * lane + k;
+                                const uint64_t vs[2] = {v, v + 1};
+                                const uint32_t code[2] = {(x >> (2 * k)) & cmask(), (x >> (2 * k + 2)) & cmask()};
+                                const bool on[2] = {(od >> k & 1u) != 0, (od >> k & 2u) != 0};
+                                uint32_t s2[2] = {s[k], s[k + 1]}, n2[2] = {n[k], n[k + 1]};
+                                odd_strings<2>(vs, code, on, s2, n2);
+                                s[k] = s2[0], s[k + 1] = s2[1];
+                                n[k] = n2[0], n[k + 1] = n2[1];
+                            }
                         }
                     }
                 }
