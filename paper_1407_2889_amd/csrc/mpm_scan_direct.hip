@@ -408,7 +408,7 @@ struct DirectScan {
                 const uint64_t deep = __ballot(max(max(n[0], n[1]), max(n[2], n[3])) > 2);
                 for (uint32_t win = 0; win < total; win += DITEMS) {
                     wave_sync();
-                    uint32_t q = incl - mine - win;  // below DITEMS: this window's place
+                    int32_t q = (int32_t)(incl - mine - win);  // of [0, DITEMS): this window's place
                     if (total <= DITEMS) {
 #pragma unroll
                         for (uint32_t k = 0; k < 4; ++k) {
@@ -424,10 +424,13 @@ struct DirectScan {
                         }
                     } else {
 #pragma unroll
-                        for (uint32_t k = 0; k < 4; ++k)
-                            for (uint32_t t = 0; t < n[k]; ++t, ++q)
-                                if (q < DITEMS)
-                                    item[q] = (s[k] + t) << 8 | (4 * lane + k);
+                        for (uint32_t k = 0; k < 4; ++k) {
+                            // (the ids of this window alone: an odd string may have thousands)
+                            const int32_t te = min((int32_t)n[k], (int32_t)DITEMS - q);
+                            for (int32_t t = max(0, -q); t < te; ++t)
+                                item[q + t] = (s[k] + (uint32_t)t) << 8 | (4 * lane + k);
+                            q += (int32_t)n[k];
+                        }
                     }
                     wave_sync();
                     // pairs of this window to write (the capacity cuts the list)

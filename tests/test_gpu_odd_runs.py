@@ -105,3 +105,34 @@ def test_odd_runs_cost(mpm):
         us[name] = min(ts)
     print(f"[odd] {us}", flush=True)
     assert us["auto"] <= 3 * us["walk"], us
+
+
+def test_odd_string_with_many_ids(mpm):
+    """A string outside the main characters given 40,000 times: its pairs take
+    80 rounds of the output buffer, each of which deals its own ids alone."""
+    rng = np.random.default_rng(9)
+    P = ACGT[rng.integers(0, 4, (10_000, 8))]
+    P[0] = np.frombuffer(b"ACGNACGT", np.uint8)
+    P = np.concatenate([P, np.tile(P[0], (40_000, 1))])
+    t = ACGT[rng.integers(0, 4, 200_000)]
+    for s in (0, 777, 4090, 4110, 100_000, len(t) - 8):
+        t[s:s + 8] = P[0]
+    want = oracle.Win(P).scan(t)
+    ix = mpm.build_ac(P, upload=True)
+    dev = dev_text(t, 3)
+    us = {}
+    for name, place in (("auto", mpm.PLACE_AUTO), ("walk", mpm.PLACE_GLOBAL)):
+        sc = mpm.Scanner(ix, len(t), len(want[0]), mpm.variant(block_threads=1024, placement=place, flags=mpm.VARIANT_DENSE))
+        a, z = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        ts = []
+        for _ in range(4):
+            a.record()
+            sc.scan_async(dev)
+            z.record()
+            torch.cuda.synchronize()
+            ts.append(a.elapsed_time(z) * 1e3)
+        us[name] = min(ts)
+        gp, gi = mpm.pairs_numpy(sc.out[: int(sc.total.item())])
+        assert np.array_equal(gp, want[0]) and np.array_equal(gi, want[1]), name
+    print(f"[odd] many ids {us}", flush=True)
+    assert us["auto"] <= 3 * us["walk"], us
