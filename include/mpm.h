@@ -142,6 +142,10 @@ typedef struct {
  * EUNSUPPORTED together, or with ILP2, SUPPLY, DENSE or the hot placement. */
 #define MPM_VARIANT_TEXT_BYTES 16u
 #define MPM_VARIANT_TEXT_LDS 32u
+/* Walk the index's own tables: with MPM_PLACE_AUTO, the placement rules of
+ * the walkers alone, without the q-gram filter or the direct-address table
+ * (explicit placements never use those). Single-text scans and batches. */
+#define MPM_VARIANT_WALK 64u
 
 /* Facts about a built index. */
 typedef struct {
@@ -379,8 +383,8 @@ typedef struct mpm_batch mpm_batch;
  * Requests under MPM_PLACE_AUTO (no flags but MPM_VARIANT_DENSE) whose set has
  * a q-gram filter and whose text has 64 bytes or more form one launch of their
  * own, whatever their indexes; its waves take pieces of equal expected time,
- * of one or more texts. (With MPM_VARIANT_ILP2, which a batch otherwise
- * ignores, a request stays with the walkers.)
+ * of one or more texts. (With another flag, MPM_VARIANT_WALK above all, a
+ * request stays with the walkers.)
  * The plan copies the request array. Host-only.
  * Errors: EINVAL, ETOOBIG, ENOMEM. */
 mpm_status mpm_batch_plan(const mpm_request *reqs, uint32_t count, mpm_batch **out);

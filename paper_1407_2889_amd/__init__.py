@@ -62,6 +62,7 @@ VARIANT_SUPPLY = 4
 VARIANT_DENSE = 8
 VARIANT_TEXT_BYTES = 16
 VARIANT_TEXT_LDS = 32
+VARIANT_WALK = 64
 
 
 class Variant(C.Structure):

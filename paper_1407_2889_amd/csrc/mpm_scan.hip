@@ -219,7 +219,7 @@ mpm_status resolve_variant(const mpm_index *ix, const mpm_variant *v, uint64_t n
     if (d.placement > MPM_PLACE_HOT)
         return fail(MPM_EINVAL, "variant: unknown placement %u", d.placement);
     if (d.flags & ~(MPM_VARIANT_NO_SWAR | MPM_VARIANT_ILP2 | MPM_VARIANT_SUPPLY | MPM_VARIANT_DENSE |
-                    MPM_VARIANT_TEXT_BYTES | MPM_VARIANT_TEXT_LDS))
+                    MPM_VARIANT_TEXT_BYTES | MPM_VARIANT_TEXT_LDS | MPM_VARIANT_WALK))
         return fail(MPM_EINVAL, "variant: unknown flags 0x%x", d.flags);
     const uint32_t text_flags = d.flags & (MPM_VARIANT_TEXT_BYTES | MPM_VARIANT_TEXT_LDS);
     if (text_flags) {

@@ -25,7 +25,7 @@ from dataclasses import dataclass
 
 import numpy as np
 
-from . import (MPM_EUNSUPPORTED, MPM_OK, MpmError, PLACE_AUTO, PLACE_GLOBAL, VARIANT_ILP2, Index,
+from . import (MPM_EUNSUPPORTED, MPM_OK, MpmError, PLACE_AUTO, PLACE_GLOBAL, VARIANT_WALK, Index,
                Variant, _check, _L, _stream_handle, _torch, build_ac, build_wm)
 
 ALGOS = ("ac", "wm")
@@ -45,11 +45,11 @@ FEATURES = ("log2_n", "log2_d", "m", "alphabet", "log2_states", "wm_mean_shift",
 
 
 def variant_struct(k: int) -> Variant:
-    """Variant k of a batched request. A batch ignores VARIANT_ILP2 but for
-    this: the request stays with the walkers, whose shapes the tuner chooses
-    between, where automatic placement alone may take the q-gram filter."""
+    """Variant k of a request. The tuner chooses between the walkers' shapes:
+    automatic placement alone may take the q-gram filter instead, whatever
+    the shape."""
     _, L, W, P = VARIANTS[k]
-    return Variant(L, W, P, 0, VARIANT_ILP2)
+    return Variant(L, W, P, 0, VARIANT_WALK)
 
 
 @dataclass
@@ -88,8 +88,7 @@ class PatternSetIndexes:
             return True
         from . import workspace_bytes
         try:
-            _, L, W, P = VARIANTS[k]
-            workspace_bytes(self.index(k), 1 << 20, Variant(L, W, P, 0, 0))
+            workspace_bytes(self.index(k), 1 << 20, variant_struct(k))
             return True
         except MpmError as e:
             if e.status == MPM_EUNSUPPORTED:
