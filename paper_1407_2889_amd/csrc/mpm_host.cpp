@@ -976,9 +976,13 @@ mpm_status workspace_sizes(const mpm_index *idx, uint64_t n, const mpm_variant *
     const uint64_t nt = (n_starts(n, idx->m) + tb - 1) / tb;
     *min_bytes = WS_HEADER_BYTES + 8 * nt;
     *full_bytes = *min_bytes;
-    if (full_bytes != min_bytes && nt && gram_takes(idx, v, n)) {
+    GramCfg g;
+    if (full_bytes != min_bytes && nt && gram_takes(idx, v, n) &&
+        (idx->max_dup < 256 || gram_config(idx, v, n, 15, &g))) {
         // the filter scan keeps its occurrences in LDS; room for the finest
-        // cut it makes of any text up to n bytes
+        // cut it makes of any text up to n bytes (what it refuses is walked:
+        // more ids per block than a wave counts, which takes 256 copies of a
+        // string and more)
         *full_bytes = std::max(*min_bytes, WS_HEADER_BYTES + 8 * (n / GRAM_CHUNK_MIN + 2));
     } else if (full_bytes != min_bytes && nt && !cfg.dense) {  // dense output stages nothing
         st = resolve_variant(idx, v, nt, &cfg);

@@ -872,8 +872,11 @@ bool gram_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, uint32_t
     // filter cost of about 18 it is the faster one (64 MiB, m = 8: d = 5000,
     // cost 16.7, filter 155 us, direct 186; d = 6000, 18.4, 201 and 189).
     g->direct = !G.ok || (ix->direct.ok && G.cost > 18.0);
-    if (g->direct)
-        return direct_config(ix, v, n, lo, g);
+    if (g->direct && direct_config(ix, v, n, lo, g))
+        return true;
+    g->direct = false;
+    if (!G.ok)
+        return false;
     const DeviceLimits lim = limits();
     // Workgroups of 1024 threads share one copy of the bits between 16 waves;
     // texts that would leave CUs without work are cut finer.

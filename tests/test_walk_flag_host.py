@@ -48,3 +48,19 @@ def test_unknown_flags_stay_refused():
         with pytest.raises(mpm.MpmError) as e:
             mpm.workspace_bytes(ix, 1 << 20, mpm.variant(64, 256, 0, 0, fl))
         assert e.value.status == mpm.MPM_EINVAL
+
+
+def test_workspace_of_a_refused_filter_scan():
+    """1.1 M copies of one string are more ids per 4 KiB block than the filter
+    and direct-address scans count: the scan is walked, so its workspace holds
+    the walkers' staging area."""
+    rng = np.random.default_rng(4)
+    few = ACGT[rng.integers(0, 4, (40, 12))]
+    many = np.concatenate([few, np.repeat(few[:1], 1_100_000, axis=0)])
+    for build in (mpm.build_ac, mpm.build_wm):
+        auto, walk = mpm.variant(16, 256), mpm.variant(16, 256, mpm.PLACE_AUTO, 0, mpm.VARIANT_WALK)
+        n = 30_000
+        ix = build(few)
+        assert mpm.workspace_bytes(ix, n, auto) < mpm.workspace_bytes(ix, n, walk)
+        ix = build(many)
+        assert mpm.workspace_bytes(ix, n, auto) == mpm.workspace_bytes(ix, n, walk)
