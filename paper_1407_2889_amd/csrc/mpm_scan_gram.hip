@@ -868,10 +868,8 @@ bool gram_takes(const mpm_index *ix, const mpm_variant *v, uint64_t n)
 bool gram_config(const mpm_index *ix, const mpm_variant *v, uint64_t n, uint32_t lo, GramCfg *g)
 {
     const mpm_index::Gram &G = ix->gram;
-    // The direct-address scan costs the same whatever the candidates; past a
-    // filter cost of about 18 it is the faster one (64 MiB, m = 8: d = 5000,
-    // cost 16.7, filter 155 us, direct 186; d = 6000, 18.4, 201 and 189).
-    g->direct = !G.ok || (ix->direct.ok && G.cost > 18.0);
+    // (where the builder kept a direct-address table it is the faster scan)
+    g->direct = ix->direct.ok;
     if (g->direct && direct_config(ix, v, n, lo, g))
         return true;
     g->direct = false;
