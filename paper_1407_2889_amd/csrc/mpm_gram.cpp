@@ -48,9 +48,16 @@ uint64_t append(std::vector<uint8_t> &img, const T *src, uint64_t count)
 // counts, share the codes' shares.
 uint32_t code_shift_of(const std::vector<uint8_t> &bytes, double *freq, double *share)
 {
-    std::fill(freq, freq + 256, 0.0);
-    for (uint8_t b : bytes)
-        freq[b] += 1.0;
+    uint32_t n[4][256];  // four counters of a byte: neighbours do not wait for each other
+    memset(n, 0, sizeof n);
+    size_t i = 0;
+    for (; i + 4 <= bytes.size(); i += 4)
+        for (int k = 0; k < 4; k++)
+            n[k][bytes[i + k]]++;
+    for (; i < bytes.size(); i++)
+        n[0][bytes[i]]++;
+    for (uint32_t b = 0; b < 256; b++)
+        freq[b] = (double)n[0][b] + n[1][b] + n[2][b] + n[3][b];
     uint32_t sh = 0;
     double best = 1e300;
     for (uint32_t s = 0; s < 7; s++) {
@@ -226,18 +233,17 @@ void build_gram(mpm_index *ix)
     // order of word, then bit), the others behind them. Offsets descend so
     // that a chain's starting positions ascend; longer strings first.
     const uint32_t wb = 2 * q - 5, nw = 1u << wb, gmask = (1u << (2 * q)) - 1u;
-    auto place = [&](uint32_t g) { return (g & (nw - 1)) * 32 + (g >> wb); };
     std::vector<uint32_t> order(ix->du);
     for (uint32_t u = 0; u < ix->du; u++)
         order[u] = u;
     if (ix->var)
         std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return S.len(a) > S.len(b); });
     std::vector<uint32_t> bits(nw, 0);
-    for (uint32_t u = 0; u < ix->du; u++)
-        for (uint32_t off = 0; off < t; off++) {
-            const uint32_t k = place((uint32_t)(head[u] >> (2 * off)) & gmask);
-            bits[k >> 5] |= 1u << (k & 31);
-        }
+    for (uint32_t u = 0; u < ix->du; u++) {
+        uint64_t h = head[u];
+        for (uint32_t off = 0; off < t; off++, h >>= 2)
+            bits[h & (nw - 1)] |= 1u << ((uint32_t)(h >> wb) & 31u);
+    }
     std::vector<uint2> words(nw);
     uint32_t ngrams = 0;
     for (uint32_t w = 0; w < nw; w++) {
@@ -250,15 +256,16 @@ void build_gram(mpm_index *ix)
     std::vector<uint8_t> plain(ix->du);
     for (uint32_t u = 0; u < ix->du; u++)
         plain[u] = !ix->var && m <= 16 && std::all_of(S.at(u), S.at(u) + m, [&](uint8_t c) { return is_main[c]; });
-    std::vector<GramEnt> ents(ngrams, GramEnt{0, 0, 0, NONE});
+    std::vector<GramEnt> ents;
     ents.reserve((uint64_t)ix->du * t);
+    ents.resize(ngrams, GramEnt{0, 0, 0, NONE});
     std::vector<uint32_t> tail(ngrams, NONE);
     for (uint32_t k = 0; k < t; k++) {
         const uint32_t off = t - 1 - k;
         for (uint32_t u : order) {
-            const uint32_t pl = place((uint32_t)(head[u] >> (2 * off)) & gmask);
-            const uint2 w = words[pl >> 5];
-            const uint32_t g = w.y + (uint32_t)__builtin_popcount(w.x & ((1u << (pl & 31)) - 1u));
+            const uint64_t h = head[u] >> (2 * off);
+            const uint2 w = words[h & (nw - 1)];
+            const uint32_t g = w.y + (uint32_t)__builtin_popcount(w.x & ((1u << ((h >> wb) & 31u)) - 1u));
             const uint32_t kl = std::min<uint32_t>(16, S.len(u));
             GramEnt e;
             e.key = (uint32_t)head[u];
@@ -276,21 +283,32 @@ void build_gram(mpm_index *ix)
         }
     }
     std::vector<uint2> strs(ix->du);
-    std::vector<uint8_t> rows;
-    rows.reserve(ix->upats.size() + 16ull * ix->du);
+    uint64_t nrows = 0;
     for (uint32_t u = 0; u < ix->du; u++) {
-        strs[u] = make_uint2((uint32_t)(rows.size() / 16), S.len(u));
-        rows.insert(rows.end(), S.at(u), S.at(u) + S.len(u));
-        rows.resize((rows.size() + 15) / 16 * 16, 0);
+        strs[u] = make_uint2((uint32_t)nrows, S.len(u));
+        nrows += (S.len(u) + 15) / 16;
     }
+    std::vector<uint8_t> rows(16 * nrows, 0);
+    for (uint32_t u = 0; u < ix->du; u++)
+        memcpy(rows.data() + 16ull * strs[u].x, S.at(u), S.len(u));
     ix->image.reserve(ix->image.size() + 4ull * (2 * bits.size() + 4 * ents.size() + 2 * strs.size()) +
                       rows.size() + 2048);
     G.q = q;
     G.cost = best;
     G.hit = 1e-9;
+    double share5[1024];  // of five codes
+    for (uint32_t g = 0; g < 1024; g++) {
+        share5[g] = 1;
+        for (uint32_t j = 0; j < 5; j++)
+            share5[g] *= share[(g >> (2 * j)) & 3u];
+    }
     for (uint32_t u = 0; u < ix->du; u++) {
+        const uint32_t k = std::min<uint32_t>(S.len(u), 25);
         double pr = 1;
-        for (uint32_t j = 0; j < std::min<uint32_t>(S.len(u), 25); j++)
+        uint32_t j = 0;
+        for (; j + 5 <= k; j += 5)
+            pr *= share5[(head[u] >> (2 * j)) & 1023u];
+        for (; j < k; j++)
             pr *= share[(head[u] >> (2 * j)) & 3u];
         G.hit += pr;
     }
