@@ -8,7 +8,9 @@ windows + 700 random; seed 3). Inputs are resident in HBM before timing.
 
 Prints one JSON line. `value` is whole-step text throughput: 2 n bytes
 scanned (n by AC, n by WM) per second. The line also carries the roofline of
-the dominant kernel (HIP events on the launch stream), the batched workload's
+the dominant kernel (HIP events on the launch stream), the rate with several
+copies of the text in turn, which kernel automatic placement runs for either
+index (the filter kernel may answer both), the batched workload's
 learned-versus-exhaustive selection (batch_* keys; 4,096 texts, 64 pattern
 sets, every policy's lists checked against the oracle's) and the CPU oracle's
 throughput on the same text (one thread per usable host CPU, at most one
@@ -596,6 +598,7 @@ def batch_selection(args) -> dict:
     autotune, learned with fallback, fixed default), every policy's lists
     checked against the oracle's. Returns the result keys."""
     import torch
+    import paper_1407_2889_amd as mpm
     import synth
     from paper_1407_2889_amd import learn, selection, tune
     t_start = time.perf_counter()
@@ -635,13 +638,31 @@ def batch_selection(args) -> dict:
         log(f"[bench] batch policy {name}: lists {'equal' if ok else 'DIFFER FROM'} the oracle's")
 
     res = selection.evaluate(b, tuner, sel, kdef, log=log, check=check)
-    res.pop("_state")
+    st = res.pop("_state")
+    # the same requests without the tuner: default variants, automatic placement
+    from paper_1407_2889_amd.batch import BatchScan
+    auto = BatchScan(st["arena"], st["offs"], st["lens"], [p.ac for p in st["pset"]],
+                     [mpm.variant(256, 512)] * len(st["lens"]), st["caps"])
+    auto.capture()
+    auto_ms = []
+    for _ in range(6):
+        a, z = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        auto.replay()
+        z.record()
+        torch.cuda.synchronize()
+        auto_ms.append(a.elapsed_time(z))
+    check("automatic", auto)
+    auto_gbps = res["text_bytes"] / (float(np.median(auto_ms[1:])) * 1e-3) / 1e9
+    auto.close()
     if gold is not None and not all(parity.values()):
         raise SystemExit(f"batched lists differ from the oracle's: {parity}")
     return {
         "learned_gbps": round(res["learned_gbps"], 2),
         "exhaustive_gbps": round(res["exhaustive_gbps"], 2),
         "default_gbps": round(res["default_gbps"], 2),
+        "walkers": True,  # the tuner and its policies choose between the walkers' variants
+        "automatic_gbps": round(auto_gbps, 2),  # no tuner, automatic placement: the filter where a set has one
         "regret": round(res["regret"], 4), "fallback_rate": round(res["fallback_rate"], 4),
         "gain_over_default": round(res["gain_over_default"], 4),
         "totals_agree": res["totals_agree"], "matches": res["matches"],
@@ -729,12 +750,20 @@ def main():
         v = mpm.variant(**variants[k])
         scanners[k] = mpm.Scanner(ix[k], n, capacity=max(1 << 20, n // 64), var=v)
 
-    # correctness guard: both algorithms report the same list
+    # correctness guard: the timed scans and the walks of both index kinds
+    # report the same list (automatic placement may answer both kinds with the
+    # same filter kernel, so the timed lists alone would compare it with itself)
     res = {k: mpm.pairs_numpy(scanners[k].scan(dev_text)) for k in ("ac", "wm")}
     M = len(res["ac"][0])
-    if not (np.array_equal(res["ac"][0], res["wm"][0]) and np.array_equal(res["ac"][1], res["wm"][1])):
-        raise SystemExit("AC and WM disagree")
-    log(f"[bench] matches={M}")
+    kernels = {}
+    for k in ("ac", "wm"):
+        v = mpm.variant(**variants[k])
+        walk = mpm.variant(**dict(variants[k], flags=variants[k].get("flags", 0) | mpm.VARIANT_WALK))
+        kernels[k] = "scan_kernel" if mpm.launch_key(ix[k], v) == mpm.launch_key(ix[k], walk) else "gram_kernel"
+        res[k + "_walk"] = mpm.pairs_numpy(mpm.scan(ix[k], dev_text, capacity=max(1 << 20, n // 64), var=walk))
+    if not all(np.array_equal(res["ac"][j], r[j]) for r in res.values() for j in (0, 1)):
+        raise SystemExit("AC and WM, or the filter and the walks, disagree")
+    log(f"[bench] matches={M}, kernels {kernels}")
 
     stream = torch.cuda.current_stream()
     # Streaming-read ceiling of this device: a coalesced read of a 1 GiB buffer.
@@ -772,6 +801,20 @@ def main():
     kms = {k: float(np.mean([a.elapsed_time(b) for a, b in ev[k]])) for k in ("ac", "wm")}
     for k in ("ac", "wm"):
         assert int(scanners[k].total.item()) == M
+    # beside the steps: copies of the text in turn, more of them than the
+    # last-level cache holds (a step finds part of its text there)
+    copies = [dev_text.clone() for _ in range(4)] + [dev_text]
+    turn = {}
+    for k in ("ac", "wm"):
+        te = [(torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True))
+              for _ in range(len(copies) * 4)]
+        for i, (a, b) in enumerate(te):
+            a.record(stream)
+            scanners[k].scan_async(copies[i % len(copies)])
+            b.record(stream)
+        torch.cuda.synchronize()
+        turn[k] = n / (float(np.mean([a.elapsed_time(b) for a, b in te[len(copies):]])) * 1e-3) / 1e9
+    del copies
     ms_step = wall / args.steps * 1e3
     gbs = {k: n / (kms[k] * 1e-3) / 1e9 for k in ("ac", "wm")}
     dom = max(kms, key=kms.get)
@@ -793,6 +836,7 @@ def main():
         "data": "synthetic",
         "config": {"workload": desc, "n_bytes": n, "d": int(P.shape[0]), "m": int(P.shape[1]),
                    "matches": M, "variants": variants},
+        "kernels": kernels,
         "ac_gbps": round(gbs["ac"], 2),
         "wm_gbps": round(gbs["wm"], 2),
         "ac_kernel_ms": round(kms["ac"], 4),
@@ -802,7 +846,11 @@ def main():
         "index_build_s": round(build_s, 3),
         "hbm_read_ceiling_gbs": round(read_ceiling, 1),
         "frac_of_read_ceiling": {k: round(gbs[k] / read_ceiling, 4) for k in ("ac", "wm")},
-        "roofline": {"bound": "hbm", "kernel": f"scan ({dom.upper()})",
+        "texts_in_turn": {"gbps": {k: round(turn[k], 2) for k in ("ac", "wm")},
+                          "frac_of_read_ceiling": {k: round(turn[k] / read_ceiling, 4) for k in ("ac", "wm")},
+                          "basis": "five copies of the text in turn, more than the last-level cache holds; "
+                                   "the steps scan one text, part of which stays there"},
+        "roofline": {"bound": "hbm", "kernel": f"{kernels[dom]} ({dom.upper()})",
                      "achieved": round(achieved, 2), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 4),
                      "traffic": recorded_traffic(args.workload, dom),

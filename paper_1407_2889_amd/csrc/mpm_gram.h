@@ -33,14 +33,10 @@ __device__ __forceinline__ uint32_t codes16(const v4u c, uint32_t sh)
     return a >> sh | b << (8 - sh) | d << (16 - sh) | e << (24 - sh);
 }
 
-// The next lane's x (lane 63: last); the previous lane's x (lane 0: first).
+// The next lane's x (lane 63: last).
 __device__ __forceinline__ uint32_t from_next(uint32_t x, uint32_t last)
 {
     return (uint32_t)__builtin_amdgcn_update_dpp((int)last, (int)x, 0x130, 0xf, 0xf, false);  // wave_shl:1
-}
-__device__ __forceinline__ uint32_t from_prev(uint32_t x, uint32_t first)
-{
-    return (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)x, 0x138, 0xf, 0xf, false);  // wave_shr:1
 }
 
 // The text (of 16 bytes or more) seen from the 16-byte boundary at or before
