@@ -357,13 +357,18 @@ void build_gram(mpm_index *ix)
         w.wide = ix->state_bytes == 4;
         w.past = (ix->var ? ix->m_max : m) - 1;
         G.off_walk = append(ix->image, &w, 1);
-        // Twice the candidates that a block should have, and one batch more:
-        // up to that a block takes about what the choice of q and t counted
-        // on. (At least an eighth of the samples instead: 256 MiB of records
-        // with poly-A tails, m = 8, 1750 -> 1480 us, but lengths 8-32 with 50
-        // strings of one head of nine A 880 -> 1220.) Wu-Manber indexes have
-        // no automaton, and their own walk takes as long on such texts.
+        // Where runs and repeats fill a block, nearly all its samples are
+        // candidates. Below three in five the candidates stay cheaper (32 MiB,
+        // us by the candidates, by the walk of a block, by the walkers: records
+        // with poly-A tails, m = 12, A^12 in the set 115, 255, 424; one string
+        // of the set over and over 38, 125, 149), unless many strings share the
+        // gram (lengths 8-32, 50 strings of one head of nine A, such records:
+        // 220, 152, 108): then past twice the candidates that a block should
+        // have, and one batch. Wu-Manber indexes have no automaton, and their
+        // own walk takes as long on such texts.
         G.crowd = (uint32_t)(64 + 2 * 4096 * rate.cand);
+        if (rate.longest <= 4 * t)
+            G.crowd = std::max(G.crowd, 2457 / t);
     }
     ix->image.resize((ix->image.size() + 255) / 256 * 256, 0);
     G.ok = 1;

@@ -298,19 +298,19 @@ struct GramScan {
     // The starting positions that a block's samples stand for, with the
     // index's automaton: each lane its own, from its first candidate to its
     // last, counted, then walked again for their pairs. For blocks with more
-    // candidates than the set's text should have (a.crowd, mpm_gram.cpp): runs
-    // of one character (poly-A tails; N, which shares G's code) and short
-    // repeats whose grams are in the set make every sample a candidate, with a
-    // chain of entries and strings to compare at each, where a walk takes a
-    // table row per byte. It is bound by the rows' round trips to L1 and L2.
-    // Measured, d = 1000, us by the candidates, by the walk here, and by the
-    // walkers of explicit placements: a tenth of the text in runs of N, G^m in
-    // the set, m = 16: 32 MiB 324, 57, 81, 256 MiB 2077, 141, 101; m = 24: 489,
-    // 87, 110, and 3215, 183, 128; all A, A^8 in the set, 32 MiB: 762, 280, 212;
-    // lengths 8-32 with 50 strings of one head of nine A, 256 MiB of A: 9608,
-    // 236, 118, of records with poly-A tails: 1504, 939, 145 (958 in the
-    // default launch shape): there the table outgrows the L1. (Four bytes per
-    // turn are 7 % faster here and cost the batch 1 % more for their code.)
+    // candidates than a.crowd (mpm_gram.cpp): runs of one character (poly-A;
+    // N, which shares G's code) and short repeats whose grams are in the set
+    // make every sample a candidate, with a chain of entries and strings to
+    // compare at each, where a walk takes a table row per byte. It is bound by
+    // the rows' round trips to L1 and L2. Measured, 128 MiB, d = 1000, us by
+    // the candidates, with the walk here, and by the walkers of explicit
+    // placements (1024 positions per lane): a tenth of the text in runs of N,
+    // G^m in the set, m = 16: 1246, 149, 84, m = 24: 1891, 194, 115; all A, A^16
+    // in the set: 3126, 1022, 2541; lengths 8-32 with 50 strings of one head of
+    // nine A, on A: 4854, 139, 85, on records with poly-A tails: 779, 487, 116
+    // (490 with 64 positions per lane): there the table outgrows the L1. (Four
+    // bytes per turn are 7 % faster here and cost the batch 1 % more for their
+    // code.)
     // Texts without such blocks: 256 MiB, m = 16, 62.1 -> 61.7; lengths 8-32,
     // 128 MiB, 62.2 -> 62.1; the batch of 256 texts 109 -> 111.
     __device__ __forceinline__ void crowded(bool direct, uint64_t base, bool any, uint32_t fs, uint32_t ls,
