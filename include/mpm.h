@@ -262,9 +262,15 @@ mpm_status mpm_workspace_bytes(const mpm_index *idx, uint64_t n, const mpm_varia
  * Sets whose strings rule out most of a text by a few characters (most sets
  * of 8 characters and more, either index kind) keep a q-gram filter in their
  * image, and MPM_PLACE_AUTO scans through it: every t-th position is looked
- * up in a bit table in LDS, and only text near a candidate is compared. Dense
- * sets of 2 to 8 characters keep a direct-address table instead: a window's
- * characters are the index of its ids. Both scans cut the text into chunks of
+ * up in a bit table in LDS, and only text near a candidate is compared; with
+ * an Aho-Corasick index, 4 KiB of text full of candidates are walked. A set
+ * has no filter when more than 64 (string, place) pairs share one gram of its
+ * strings' heads, as 66 strings with a common head of 10 to 12 characters do,
+ * however large the set: its scans walk the tables. Dense sets of 2 to 8
+ * characters keep a direct-address table instead: a window's characters are
+ * the index of its ids. Builders make these tables for every set that can
+ * have them (1,000 strings of 16 characters: 0.3 of 2 ms, 0.2 MB of the
+ * image), also where a caller then uses explicit placements alone. Both scans cut the text into chunks of
  * their own, whatever lane_bytes and block_threads say; a workspace smaller
  * than mpm_workspace_bytes may make the scan walk the tables instead. The list
  * is the same.

@@ -28,10 +28,11 @@
 //
 // Measured against the dense-output walkers (EST-shaped text, m = 8, us, before
 // and after): 64 MiB, d = 10k 398 -> 189, d = 100k (92 M pairs) 856 -> 368;
-// 16 MiB, d = 30k 492 -> 65; 4 MiB, d = 30k 133 -> 39. Vector issue bounds it:
-// sixteen waves of a CU share four SIMDs, an instruction takes one of them four
-// cycles, and a round of 256 positions has 200 to 300, besides what its pairs
-// take to gather and write (d = 100k with odd strings looked up round by round,
+// 16 MiB, d = 30k 492 -> 65; 4 MiB, d = 30k 133 -> 39. No unit alone bounds it
+// (d = 100k, counters): sixteen waves of a CU share four SIMDs, an instruction
+// takes one of them four cycles, and a round of 256 positions has 200 to 300,
+// 48 % of the issue slots; the L2 serves 60 M requests, an id per pair, about
+// 58 % of its rate; the LDS is active a quarter of the time (d = 100k with odd strings looked up round by round,
 // four runs of ids in flight and branches around each item: 390). Keeping the
 // first pass's strings in registers (64 unrolled rounds) or their id counts as
 // scalar thresholds measured 586 to 860 us for d = 100k.
