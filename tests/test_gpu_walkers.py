@@ -73,6 +73,7 @@ def test_sweep_walkers(mpm, sweep_text, golden, d, m):
     for algo in ("ac", "wm"):
         ix = build(mpm, algo, ps.patterns)
         for v in (mpm.variant(1024, 1024, flags=mpm.VARIANT_WALK),
+                  mpm.variant(1024, 1024, mpm.PLACE_GLOBAL),
                   mpm.variant(block_threads=1024, flags=mpm.VARIANT_WALK | mpm.VARIANT_DENSE)):
             print(f"[walk] sweep d={d} m={m} {algo} {v}", flush=True)
             got = mpm.scan(ix, dev, capacity=g["total"], var=v)
