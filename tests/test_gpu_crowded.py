@@ -3,9 +3,9 @@ shares G's 2-bit code, and short repeats), through automatic placement,
 against the oracle element by element: runs shorter and longer than a 4 KiB
 block, at the text's start and end and at odd alignments, blocks before and
 after a run, lists that fit the LDS and lists that do not, cut lists, strings
-longer than a lane's range, repeated strings and mixed lengths. Blocks whose
-candidates take more work than a walk are walked with the automaton
-(Aho-Corasick indexes), the others are not, and the list is one."""
+longer than a lane's range, repeated strings and mixed lengths. Blocks with
+candidates almost everywhere are walked with the automaton (Aho-Corasick
+indexes), the others are not, and the list is one."""
 
 import numpy as np
 import pytest
@@ -160,9 +160,9 @@ def test_runs_batched(mpm):
 @pytest.mark.parametrize("m", [8, 16, 24])
 def test_runs_cost_about_a_walk(mpm, m):
     """A tenth of the text in runs of N, poly-G in the set: every sample of the
-    runs is a candidate. A block gives up after about a walk's work and is
-    walked, and the next tries come at growing distances, so the scan takes at
-    most about twice the walkers' time."""
+    runs is a candidate. Such blocks are walked, through L1 and L2 where the
+    walkers have LDS and by the few waves that hold a run, so the scan takes
+    about the walkers' time and not three to five times that."""
     n = 32 << 20
     g = torch.Generator(device="cuda")
     g.manual_seed(5)
